@@ -156,7 +156,7 @@ gm_status gm_gate_bwd_budget(const float* dgate, const float* soft, int64_t n, f
  * gm_masked_linear_fwd (op = GM_OP_FWD) or gm_masked_linear_bwd
  * (op = GM_OP_BWD) needs for the given shape.  No device work.  The forward
  * needs one only for launches of few output tiles (at most 128 tiles of
- * 256 x 256, e.g. T = 512 with d_out = 5120), where it splits K: then
+ * 256 x 256, e.g. T = 512 with d_out = 5120), where it may split K: then
  * ksplit * T * d_out fp32 for the partial tiles (ksplit <= 8); otherwise 0.
  *   bytes: HOST pointer, required.
  */
@@ -178,10 +178,10 @@ gm_status gm_workspace_size(int op, int64_t T, int64_t d_in, int64_t d_out, int3
  *   d_out a multiple of g_out; each of X, W, Y (T rounded up to a multiple
  *   of 8) below 2^30 - 2^22 elements.  Mask values must be finite and >= 0
  *   (not checked).
- *   ws / ws_bytes: optional workspace (16-byte aligned).  NULL: the GEMM
- *   runs unsplit.  Otherwise at least gm_workspace_size(GM_OP_FWD, ...) bytes
- *   (GM_ERR_WORKSPACE if smaller), and shapes with few output tiles split K
- *   over several blocks whose fp32 partial tiles are added in a fixed order
+ *   ws / ws_bytes: optional workspace (16-byte aligned).  NULL: no
+ *   tile's K range is split over blocks.  Otherwise at least gm_workspace_size(GM_OP_FWD, ...) bytes
+ *   (GM_ERR_WORKSPACE if smaller), and shapes with few output tiles may split
+ *   K over several blocks whose fp32 partial tiles are added in a fixed order
  *   before the one rounding to bf16 (the same Y up to fp32 summation order;
  *   deterministic for a given shape).  The workspace is scratch: its contents
  *   are not used across calls.
@@ -250,8 +250,9 @@ gm_status gm_pack_rows(const uint16_t* W, const float* mask, int64_t d_in, int64
 /*
  * gm_packed_linear_fwd -- forward of a pruned linear from its packed export
  * (the inference path of the pruned model): the same Y as gm_masked_linear_fwd
- * with the mask that gm_pack_rows consumed.  Built for decode-sized T (reads
- * every kept weight once per 16 tokens); any T >= 1 is accepted.
+ * with the mask that gm_pack_rows consumed, for any T >= 1: up to 16 tokens read
+ * every kept weight once; more run the GEMM on the pieces (tiles with fractional
+ * selectors compute their rows in fp32 instead, at the decode kernel's rate).
  *   X [T, d_in] bf16; Wp, chunk, scale, rowptr as written by gm_pack_rows,
  *   which must have held every kept group (rowptr[d_out] <= its capacity);
  *   g is the width of the exported pieces (the group width; a square export

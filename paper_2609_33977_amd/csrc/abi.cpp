@@ -126,6 +126,56 @@ size_t fwd_workspace(int64_t T, int64_t d_in, int64_t d_out, int32_t g) {
   return ks > 1 ? round_up(size_t(ks) * size_t(T) * size_t(d_out) * sizeof(float), 256) : 0;
 }
 
+// Tile of the forward GEMM: the one with the lowest estimated time.  A launch
+// runs rounds of 256 blocks (one per CU); a block takes a fixed time (launch,
+// mask bits, pipeline fill, epilogue) and a time per 32-deep K slice, and a
+// last round that is partly empty costs half a round plus half its fill (a
+// launch of less than one round costs a whole one).
+// Measured (4096 x 4096, half the groups kept): 256 x 256 tiles 15 us + 0.66
+// us per slice; 256 x 128 (K over two wave groups) 14 us + 0.42; 128 x 128
+// (same) 9 us + 0.25; a K split over blocks adds a reduction of 4 us and 8
+// bytes per output and share (mostly cached: 15 TB/s).  The model picks the
+// fastest or within 3 % of it at T = 128 .. 4096 on 1024^2, 2816 x 2056, 4096^2,
+// 11008 x 4096 (both ways) and the LLaMA-2-13B shapes: e.g. T = 2048 at 4096^2
+// 65 us in 256 x 128 tiles (256 x 256 split in two: 73), T = 1024 41 us in 128 x
+// 128 tiles (split in four: 50), T = 4096 98 us in 256 x 256 tiles (125).
+struct FwdPlan {
+  gm::FwdTile tile;
+  int ks;
+};
+
+int64_t fwd_rounds_ns(int64_t blocks, int64_t block_ns) {
+  const int64_t full = blocks / 256, rest = blocks % 256;
+  if (full == 0) return block_ns;
+  return full * block_ns + (rest ? block_ns / 2 + block_ns * rest / 512 : 0);
+}
+
+bool fwd_tile_fits(gm::FwdTile tile, int64_t d_in, int32_t g, int32_t g_out, bool packed) {
+  if (tile == gm::FwdTile::k128x128) return true;
+  if (g < 32 || (packed && g < 64)) return tile == gm::FwdTile::k256x256 && !packed;
+  if (g_out != 1 || (tile == gm::FwdTile::k256x256 && !packed)) return true;
+  return d_in / g <= gm::fwd_max_groups(g, packed, tile == gm::FwdTile::k256x128);
+}
+
+// ks: shares of the 256 x 256 tile's K range (1 without a workspace).
+FwdPlan fwd_plan(int64_t T, int64_t d_in, int64_t d_out, int32_t g, int32_t g_out, bool packed, int ks) {
+  using gm::FwdTile;
+  const int64_t slices = d_in / 32;
+  auto tiles = [&](int64_t bm, int64_t bn) { return ((d_out + bm - 1) / bm) * ((T + bn - 1) / bn); };
+  FwdPlan best{FwdTile::k128x128, 1};
+  int64_t best_ns = fwd_rounds_ns(tiles(128, 128), 9000 + 250 * slices);
+  if (fwd_tile_fits(FwdTile::k256x128, d_in, g, g_out, packed)) {
+    const int64_t ns = fwd_rounds_ns(tiles(256, 128), 14000 + 420 * slices);
+    if (ns < best_ns) best = {FwdTile::k256x128, 1}, best_ns = ns;
+  }
+  if (fwd_tile_fits(FwdTile::k256x256, d_in, g, g_out, packed)) {
+    int64_t ns = fwd_rounds_ns(tiles(256, 256) * ks, 15000 + 660 * slices / ks);
+    if (ks > 1) ns += 4000 + ks * T * d_out * 8 / 15000;
+    if (ns < best_ns) best = {FwdTile::k256x256, ks}, best_ns = ns;
+  }
+  return best;
+}
+
 // Workspace of the backward, each part 256-byte aligned, over NL = d_in / lc
 // list columns of lc = max(g, 64) input columns (nsub = lc / g groups each):
 //   colcount [NL] int32 | colsoft [NL] int32 | rows [NL * d_out + 128] int32 |
@@ -364,9 +414,9 @@ GM_EXPORT gm_status gm_masked_linear_fwd(const uint16_t* X, const uint16_t* W, c
   const int t = int(T), di = int(d_in), dout = int(d_out);
   if (T <= kDecodeTokens && d_in / g <= gm::gemv_max_groups_per_row())
     return from_hip(gm::launch_gemv_inplace(X, W, mask, t, di, dout, g, g_out, Y, stream));
-  // Without a workspace the forward runs unsplit (the same Y up to fp32 summation order).
-  const int ks = ws && need ? fwd_splits(T, d_in, d_out, g) : 1;
-  return from_hip(gm::launch_fwd(X, W, mask, t, di, dout, g, g_out, Y, ks, static_cast<float*>(ws), stream));
+  // Without a workspace no tile's K range is split over blocks (the same Y up to fp32 summation order).
+  const FwdPlan p = fwd_plan(T, d_in, d_out, g, g_out, false, ws && need ? fwd_splits(T, d_in, d_out, g) : 1);
+  return from_hip(gm::launch_fwd(X, W, mask, t, di, dout, g, g_out, Y, p.tile, p.ks, static_cast<float*>(ws), stream));
 }
 
 namespace {
@@ -499,6 +549,11 @@ GM_EXPORT gm_status gm_packed_linear_fwd(const uint16_t* X, const uint16_t* Wp, 
       !aligned16(Y))
     return GM_ERR_ALIGN;
   if (gm_status st = check_device()) return st;
+  if (T > kDecodeTokens) {
+    const FwdPlan p = fwd_plan(T, d_in, d_out, g, 1, true, 1);
+    return from_hip(gm::launch_fwd_packed(X, Wp, chunk, scale, rowptr, int(T), int(d_in), int(d_out), g, Y, p.tile,
+                                          stream));
+  }
   return from_hip(
       gm::launch_gemv_packed(X, Wp, chunk, scale, rowptr, int(T), int(d_in), int(d_out), g, Y, stream));
 }

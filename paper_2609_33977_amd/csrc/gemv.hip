@@ -15,28 +15,9 @@
 #include "gm_device.h"
 #include "gm_launch.h"
 #include "gm_pipe.h"
+#include "gm_rows.h"
 
 namespace gm {
-
-typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
-
-// Dot product of two vectors of 8 bf16 with fp32 accumulation (v_dot2_f32_bf16).
-// The bf16 pairs are moved out of the 32-bit lanes with memcpy: a bit_cast of
-// a subscripted vector element inside this unrolled loop was folded to element
-// 0 by the compiler (every step used the first pair).
-__device__ __forceinline__ float dot8_bf16(u32x4 w, u32x4 x) {
-  const uint32_t wa[4] = {w.x, w.y, w.z, w.w};
-  const uint32_t xa[4] = {x.x, x.y, x.z, x.w};
-  float acc = 0.0f;
-#pragma unroll
-  for (int q = 0; q < 4; ++q) {
-    bf16x2 a, b;
-    __builtin_memcpy(&a, &wa[q], sizeof(a));
-    __builtin_memcpy(&b, &xa[q], sizeof(b));
-    acc = __builtin_amdgcn_fdot2_f32_bf16(a, b, acc, false);
-  }
-  return acc;
-}
 
 constexpr int kMaxGroupsPerRow = 1024;  // G_in limit of the in-place variant's per-wave list
 
@@ -62,11 +43,11 @@ __global__ __launch_bounds__(256) void gemv_kernel(const uint16_t* __restrict__ 
   const int e = (lane % lanes_per_group) * 8;
   const int ntok = min(TB, T - t0);
 
+  float acc[TB];
   int nk;
-  int64_t pbase = 0;
   if constexpr (PACKED) {
-    pbase = rowptr[o];
-    nk = rowptr[o + 1] - int(pbase);
+    const int p = rowptr[o];
+    packed_row<TB>(X, Wp, chunk, scale, p, rowptr[o + 1] - p, t0, ntok, d_in, g, lane, acc);
   } else {
     // Compact this row's kept groups into the wave's LDS list, in column order.
     nk = 0;
@@ -85,59 +66,37 @@ __global__ __launch_bounds__(256) void gemv_kernel(const uint16_t* __restrict__ 
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
     __builtin_amdgcn_wave_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-  }
-
-  float acc[TB];
 #pragma unroll
-  for (int t = 0; t < TB; ++t) acc[t] = 0.0f;
-
-  for (int k0 = 0; k0 < nk; k0 += 2 * gps) {
-    const int ka = k0 + slot;
-    const int kb = k0 + gps + slot;
-    int va = 0, vb = 0;
-    float ma = 0.0f, mb = 0.0f;
-    u32x4 wa = zero16(), wb = zero16();
-    if (ka < nk) {
-      if constexpr (PACKED) {
-        va = chunk[pbase + ka];
-        ma = scale[pbase + ka];
-        wa = ld16(Wp + (pbase + ka) * g + e);
-      } else {
+    for (int t = 0; t < TB; ++t) acc[t] = 0.0f;
+    for (int k0 = 0; k0 < nk; k0 += 2 * gps) {
+      const int ka = k0 + slot, kb = k0 + gps + slot;
+      int va = 0, vb = 0;
+      float ma = 0.0f, mb = 0.0f;
+      u32x4 wa = zero16(), wb = zero16();
+      if (ka < nk) {
         va = s_v[wv][ka];
         ma = s_m[wv][ka];
         wa = ld16(W + int64_t(o) * d_in + int64_t(va) * g + e);
       }
-    }
-    if (kb < nk) {
-      if constexpr (PACKED) {
-        vb = chunk[pbase + kb];
-        mb = scale[pbase + kb];
-        wb = ld16(Wp + (pbase + kb) * g + e);
-      } else {
+      if (kb < nk) {
         vb = s_v[wv][kb];
         mb = s_m[wv][kb];
         wb = ld16(W + int64_t(o) * d_in + int64_t(vb) * g + e);
       }
-    }
 #pragma unroll
-    for (int t = 0; t < TB; ++t) {
-      if (t < ntok) {
-        const uint16_t* xr = X + int64_t(t0 + t) * d_in + e;
-        float p = 0.0f;
-        if (ka < nk) p += ma * dot8_bf16(wa, ld16(xr + int64_t(va) * g));
-        if (kb < nk) p += mb * dot8_bf16(wb, ld16(xr + int64_t(vb) * g));
-        acc[t] += p;
+      for (int t = 0; t < TB; ++t) {
+        if (t < ntok) {
+          const uint16_t* xr = X + int64_t(t0 + t) * d_in + e;
+          float p = 0.0f;
+          if (ka < nk) p += ma * dot8_bf16(wa, ld16(xr + int64_t(va) * g));
+          if (kb < nk) p += mb * dot8_bf16(wb, ld16(xr + int64_t(vb) * g));
+          acc[t] += p;
+        }
       }
     }
+    wave_sums(acc);
   }
 
-#pragma unroll
-  for (int t = 0; t < TB; ++t) {
-    float s = acc[t];
-#pragma unroll
-    for (int d = 32; d >= 1; d >>= 1) s += __shfl_xor(s, d);
-    acc[t] = s;
-  }
   if (lane == 0) {
 #pragma unroll
     for (int t = 0; t < TB; ++t)

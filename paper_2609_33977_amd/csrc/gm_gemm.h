@@ -113,7 +113,7 @@ template <int MB, int NB, bool A_KM, bool B_KM, int CA, int CB, int PER_STAGE, i
 __device__ __forceinline__ void gemm_mainloop(u32x4 (*As)[ABUF], u32x4 (*Bs)[BBUF], int nst, int a0, int b0, int lane,
                                               f32x4 (&acc)[MB][NB], Prepare&& prepare, Issue&& issue,
                                               Landed&& landed, BHook&& bhook, Live live = Live{}) {
-  static_assert(PER_STAGE <= NB, "copies are interleaved with the NB MFMAs of one row");
+  constexpr int CPN = (PER_STAGE + NB - 1) / NB;  // copies issued beside each column's MFMAs after the barrier
   static_assert(RA >= 1 && RA <= MB, "rows after the barrier");
   // loads issued after the copies of the slice being waited for: the later
   // slices' copies and the XTRA loads of every prepare() since
@@ -172,7 +172,9 @@ __device__ __forceinline__ void gemm_mainloop(u32x4 (*As)[ABUF], u32x4 (*Bs)[BBU
       for (int r = 0; r < RA; ++r)
         if ((lv >> (MB - RA + r)) & 1u) mfma_at<FIRST, MB, NB>(MB - RA + r, nb, ar[r], bf[nb], acc);
       __builtin_amdgcn_sched_barrier(0);
-      if (nb < PER_STAGE) issue(kt + STAGES, nb);
+#pragma unroll
+      for (int p = nb * CPN; p < (nb + 1) * CPN; ++p)
+        if (p < PER_STAGE) issue(kt + STAGES, p);
       bf[nb] = B_KM ? km_frag(Bn, b0 + nb * 16, lane) : mn_frag<CB>(Bn, b0 + nb * 16, lane);
       __builtin_amdgcn_sched_barrier(0);
     }
@@ -239,6 +241,58 @@ __device__ __forceinline__ void store_tile_rows(const f32x4 (&acc)[MB][NB], char
   for (int k = 0; k < 256 * CPR / (64 * NW); ++k) {
     const int e = k * 64 * NW + tid, n = e / CPR, c = e % CPR;
     const u32x4 v = *reinterpret_cast<const u32x4*>(row_base(n) + ((c ^ (n & (CPR - 1))) << 4));
+    if (r0 + n < rlim && c0 + 8 * c < clim)
+      __builtin_nontemporal_store(v, reinterpret_cast<u32x4*>(out + int64_t(r0 + n) * ld + c0 + 8 * c));
+  }
+}
+
+// The same output for a tile whose K range was split over two wave groups
+// kg = 0, 1 (each 2 (m) x NW/4 (n) waves holding the whole BM x BN tile): each
+// wave hands the other group's wave with the same fragments half of them
+// through LDS (fragment rows [0, MB/2) to group 0, the rest to group 1, HC rows
+// at a time), adds the half it got to its own (two addends: the same sum
+// whichever is first), and the bf16 rows go out as above.  xch: NW HC NB KiB;
+// rows: 2 BM BN bytes (another buffer).
+template <int BM, int BN, int MB, int NB, int NW, int HC>
+__device__ __forceinline__ void store_tile_ksum2(const f32x4 (&acc)[MB][NB], f32x4* xch, char* rows, int kg, int wg,
+                                                 int wm, int wn, int tid, int lane, uint16_t* __restrict__ out,
+                                                 int64_t ld, int r0, int rlim, int c0, int clim) {
+  constexpr int NG = NW / 2, H = MB / 2, CPR = BM / 8;
+  static_assert(MB * 32 == BM && NB * 16 * (NG / 2) == BN && MB % 2 == 0 && H % HC == 0, "tile shape");
+  auto finish = [&](auto own) {
+    constexpr int O = decltype(own)::value;  // fragment rows this group keeps: [O, O + H)
+#pragma unroll
+    for (int h = 0; h < H; h += HC) {
+      __syncthreads();  // every wave has left its K-loop (its copies drained), or read the previous rows
+#pragma unroll
+      for (int q = 0; q < HC; ++q)
+#pragma unroll
+        for (int nb = 0; nb < NB; ++nb)
+          xch[(((kg * NG + wg) * HC + q) * NB + nb) * 64 + lane] = acc[(H - O) + h + q][nb];
+      __syncthreads();
+#pragma unroll
+      for (int q = 0; q < HC; ++q)
+#pragma unroll
+        for (int nb = 0; nb < NB; ++nb) {
+          const f32x4 sum = acc[O + h + q][nb] + xch[((((1 - kg) * NG + wg) * HC + q) * NB + nb) * 64 + lane];
+          const int m = wm * (BM / 2) + (O + h + q) * 16 + 4 * (lane >> 4);
+          const int n = wn * NB * 16 + nb * 16 + (lane & 15);
+          uint2 w;
+          w.x = pack_bf16x2(sum[0], sum[1]);
+          w.y = pack_bf16x2(sum[2], sum[3]);
+          *reinterpret_cast<uint2*>(rows + n * (2 * BM) + (((m >> 3) ^ (n & (CPR - 1))) << 4) + ((m >> 2) & 1) * 8) = w;
+        }
+    }
+    __syncthreads();
+  };
+  if (kg == 0)  // uniform per wave; both sides meet the same number of barriers
+    finish(std::integral_constant<int, 0>{});
+  else
+    finish(std::integral_constant<int, H>{});
+#pragma unroll 4
+  for (int k = 0; k < BN * CPR / (64 * NW); ++k) {
+    const int e = k * 64 * NW + tid, n = e / CPR, c = e % CPR;
+    const u32x4 v = *reinterpret_cast<const u32x4*>(rows + n * (2 * BM) + ((c ^ (n & (CPR - 1))) << 4));
     if (r0 + n < rlim && c0 + 8 * c < clim)
       __builtin_nontemporal_store(v, reinterpret_cast<u32x4*>(out + int64_t(r0 + n) * ld + c0 + 8 * c));
   }

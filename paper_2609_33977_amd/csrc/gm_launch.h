@@ -31,10 +31,23 @@ hipError_t launch_gemv_packed(const uint16_t* X, const uint16_t* Wp, const int* 
                               const int* rowptr, int T, int d_in, int d_out, int g, uint16_t* Y, hipStream_t s);
 int gemv_max_groups_per_row();
 
-// ksplit > 1 splits each tile's K range over that many blocks, which store fp32
+// Output tiles of the forward GEMM, rows of Y's columns (o) x tokens; the two
+// 128-token tiles split K over two wave groups inside the block.
+enum class FwdTile { k256x256, k256x128, k128x128 };
+
+// Selectors per row that the 256-row tiles have LDS for beside their rings (1 x g groups; the in-place 256 x 256
+// tile and the 128 x 128 tiles hold every row the library accepts).
+constexpr int fwd_max_groups(int g, bool packed, bool half) {
+  return packed && half && 16384 / g > 128 ? 128 : 16384 / g;
+}
+
+// ksplit > 1 (256 x 256 tiles) splits each tile's K range over that many blocks, which store fp32
 // partial tiles into part [ksplit][T][d_out]; a second kernel adds them in order.
 hipError_t launch_fwd(const uint16_t* X, const uint16_t* W, const float* mask, int T, int d_in, int d_out, int g,
-                      int go, uint16_t* Y, int ksplit, float* part, hipStream_t s);
+                      int go, uint16_t* Y, FwdTile tile, int ksplit, float* part, hipStream_t s);
+hipError_t launch_fwd_packed(const uint16_t* X, const uint16_t* Wp, const int* chunk, const float* scale,
+                             const int* rowptr, int T, int d_in, int d_out, int g, uint16_t* Y, FwdTile tile,
+                             hipStream_t s);
 // With colcount set, the launch also builds the column lists (as launch_col_lists).
 hipError_t launch_dgate(const uint16_t* dY, const uint16_t* X, const uint16_t* W, int T, int d_in, int d_out, int g,
                         int go, float* dgate, uint16_t* dYt, int ldt, const float* mask, int nsub, int* colcount,

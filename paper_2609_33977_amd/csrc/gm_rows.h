@@ -1,0 +1,87 @@
+// One output row of the packed export on one wave: dot products straight from
+// the pieces, shared by the row-per-wave decode kernel and by the tiles of the
+// packed GEMM that hold pieces it has no matrix form for.
+#pragma once
+
+#include "gm_device.h"
+
+namespace gm {
+
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+
+// Dot product of two vectors of 8 bf16 with fp32 accumulation (v_dot2_f32_bf16).
+// The bf16 pairs are moved out of the 32-bit lanes with memcpy: a bit_cast of
+// a subscripted vector element inside this unrolled loop was folded to element
+// 0 by the compiler (every step used the first pair).
+__device__ __forceinline__ float dot8_bf16(u32x4 w, u32x4 x) {
+  const uint32_t wa[4] = {w.x, w.y, w.z, w.w};
+  const uint32_t xa[4] = {x.x, x.y, x.z, x.w};
+  float acc = 0.0f;
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    bf16x2 a, b;
+    __builtin_memcpy(&a, &wa[q], sizeof(a));
+    __builtin_memcpy(&b, &xa[q], sizeof(b));
+    acc = __builtin_amdgcn_fdot2_f32_bf16(a, b, acc, false);
+  }
+  return acc;
+}
+
+// Sums over the wave of TB per-lane values, left in every lane.
+template <int TB>
+__device__ __forceinline__ void wave_sums(float (&acc)[TB]) {
+#pragma unroll
+  for (int t = 0; t < TB; ++t) {
+    float s = acc[t];
+#pragma unroll
+    for (int d = 32; d >= 1; d >>= 1) s += __shfl_xor(s, d);
+    acc[t] = s;
+  }
+}
+
+// acc[t] = sum over pieces p0 .. p0 + nk - 1 of scale * (piece . X[t0 + t, its columns]), t < ntok <= TB, in fp32
+// (pieces in any order; columns past d_in are skipped).
+template <int TB>
+__device__ __forceinline__ void packed_row(const uint16_t* __restrict__ X, const uint16_t* __restrict__ Wp,
+                                           const int* __restrict__ chunk, const float* __restrict__ scale, int64_t p0,
+                                           int nk, int t0, int ntok, int d_in, int g, int lane, float (&acc)[TB]) {
+  const int lanes_per_group = g >> 3;
+  const int gps = 64 / lanes_per_group;  // pieces per wave step (>= 1 for g <= 512)
+  const int slot = lane / lanes_per_group;
+  const int e = (lane % lanes_per_group) * 8;
+  const int G_in = d_in / g;
+#pragma unroll
+  for (int t = 0; t < TB; ++t) acc[t] = 0.0f;
+  for (int k0 = 0; k0 < nk; k0 += 2 * gps) {
+    int v[2];
+    float m[2];
+    u32x4 w[2];
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+      const int k = k0 + q * gps + slot;
+      v[q] = k < nk ? chunk[p0 + k] : -1;
+      m[q] = 0.0f;
+      w[q] = zero16();
+      if (v[q] >= 0 && v[q] < G_in) {
+        m[q] = scale[p0 + k];
+        w[q] = ld16(Wp + (p0 + k) * g + e);
+      } else {
+        v[q] = -1;
+      }
+    }
+#pragma unroll
+    for (int t = 0; t < TB; ++t) {
+      if (t < ntok) {
+        const uint16_t* xr = X + int64_t(t0 + t) * d_in + e;
+        float p = 0.0f;
+#pragma unroll
+        for (int q = 0; q < 2; ++q)
+          if (v[q] >= 0) p += m[q] * dot8_bf16(w[q], ld16(xr + int64_t(v[q]) * g));
+        acc[t] += p;
+      }
+    }
+  }
+  wave_sums(acc);
+}
+
+}  // namespace gm
