@@ -126,12 +126,9 @@ size_t fwd_workspace(int64_t T, int64_t d_in, int64_t d_out, int32_t g) {
   return ks > 1 ? round_up(size_t(ks) * size_t(T) * size_t(d_out) * sizeof(float), 256) : 0;
 }
 
-// Tile of the forward GEMM: the one with the lowest estimated time.  A launch
-// runs rounds of 256 blocks (one per CU); a block takes a fixed time (launch,
-// mask bits, pipeline fill, epilogue) and a time per 32-deep K slice, and a
-// last round that is partly empty costs half a round plus half its fill (a
-// launch of less than one round costs a whole one).
-// Measured (4096 x 4096, half the groups kept): 256 x 256 tiles 15 us + 0.66
+// Tile of the forward GEMM: the one with the lowest estimated time, rounds of
+// blocks (gm::rounds_ns) that take a fixed time (launch, mask bits, pipeline
+// fill, epilogue) and a time per 32-deep K slice.  Measured (4096 x 4096, half the groups kept): 256 x 256 tiles 15 us + 0.66
 // us per slice; 256 x 128 (K over two wave groups) 14 us + 0.42; 128 x 128
 // (same) 9 us + 0.25; a K split over blocks adds a reduction of 4 us and 8
 // bytes per output and share (mostly cached: 15 TB/s).  The model picks the
@@ -143,12 +140,6 @@ struct FwdPlan {
   gm::FwdTile tile;
   int ks;
 };
-
-int64_t fwd_rounds_ns(int64_t blocks, int64_t block_ns) {
-  const int64_t full = blocks / 256, rest = blocks % 256;
-  if (full == 0) return block_ns;
-  return full * block_ns + (rest ? block_ns / 2 + block_ns * rest / 512 : 0);
-}
 
 bool fwd_tile_fits(gm::FwdTile tile, int64_t d_in, int32_t g, int32_t g_out, bool packed) {
   if (tile == gm::FwdTile::k128x128) return true;
@@ -163,13 +154,13 @@ FwdPlan fwd_plan(int64_t T, int64_t d_in, int64_t d_out, int32_t g, int32_t g_ou
   const int64_t slices = d_in / 32;
   auto tiles = [&](int64_t bm, int64_t bn) { return ((d_out + bm - 1) / bm) * ((T + bn - 1) / bn); };
   FwdPlan best{FwdTile::k128x128, 1};
-  int64_t best_ns = fwd_rounds_ns(tiles(128, 128), 9000 + 250 * slices);
+  int64_t best_ns = gm::rounds_ns(tiles(128, 128), 9000 + 250 * slices);
   if (fwd_tile_fits(FwdTile::k256x128, d_in, g, g_out, packed)) {
-    const int64_t ns = fwd_rounds_ns(tiles(256, 128), 14000 + 420 * slices);
+    const int64_t ns = gm::rounds_ns(tiles(256, 128), 14000 + 420 * slices);
     if (ns < best_ns) best = {FwdTile::k256x128, 1}, best_ns = ns;
   }
   if (fwd_tile_fits(FwdTile::k256x256, d_in, g, g_out, packed)) {
-    int64_t ns = fwd_rounds_ns(tiles(256, 256) * ks, 15000 + 660 * slices / ks);
+    int64_t ns = gm::rounds_ns(tiles(256, 256) * ks, 15000 + 660 * slices / ks);
     if (ks > 1) ns += 4000 + ks * T * d_out * 8 / 15000;
     if (ns < best_ns) best = {FwdTile::k256x256, ks}, best_ns = ns;
   }

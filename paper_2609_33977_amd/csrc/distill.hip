@@ -18,7 +18,7 @@
 // token and vocabulary entry) costs one write and one read of HBM instead of
 // recomputing both passes' logits in the backward, which is the cheaper side
 // on a GPU with this much memory and bandwidth.
-#include "gm_gemm.h"
+#include "gm_wt.h"
 #include "gm_launch.h"
 
 #include <math.h>
@@ -31,7 +31,7 @@ constexpr int kLmStats = 5;     // m_T, s_T, m_S, s_S, c per token and vocabular
 // MFMA rows of a wave tile issued after each slice's barrier in the K-loop:
 // four measured 1.6 % faster for the backward GEMM and 0.6 % slower for the
 // forward one (whose epilogue dominates), so the forward keeps one.
-constexpr int kLmFwdRowsAfter = 1, kLmBwdRowsAfter = 4;
+constexpr int kLmFwdRowsAfter = 1;
 
 // (m, s) <- merge of two (max, sum of exp(x - max)) summaries; an empty one has m = -inf, s = 0.
 __device__ __forceinline__ void lse_merge(float& m, float& s, float m2, float s2) {
@@ -319,60 +319,12 @@ __global__ __launch_bounds__(256) void distill_dz_kernel(const float* __restrict
   st16(dz + int64_t(t) * ldv + v, out);
 }
 
-// dH[t, j] = sum_v dZ[t, v] W[v, j]: tile 256 (j) x 256 (t), K = v.  W is
-// [V, d] with K as its row index (MN-major tile, transposing reads); dZ rows
-// are K-contiguous (K-major tile).  Waves 2 (j) x 4 (t).
+// dH[t, j] = sum_v dZ[t, v] W[v, j] (K = v, dZ rows padded with zeros to ldv).
+template <int BM, int BN, int KS>
 __global__ __launch_bounds__(64 * kLmWaves) void lmhead_bwd_kernel(const uint16_t* __restrict__ dz, int ldv,
                                                                   const uint16_t* __restrict__ W, int N, int d,
                                                                   int V, uint16_t* __restrict__ dH) {
-  constexpr int NW = kLmWaves, WN = NW / 2;
-  constexpr int BM = 256, BN = 256, MB = 8, NB = BN / WN / 16;
-  constexpr int PER_STAGE = 32 / NW, CA = PER_STAGE / 2, STAGES = 4;
-  __shared__ u32x4 As[STAGES][kBK * BM / 8];
-  __shared__ u32x4 Bs[STAGES][BN * 4];
-
-  const int tid = threadIdx.x, lane = tid & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int wm = wave / WN, wn = wave % WN;
-  const int tiles_m = (d + BM - 1) / BM, tiles_n = (N + BN - 1) / BN;
-  int tm, tn;
-  tile_coords(gridDim.x, tiles_m, tiles_n, tm, tn);
-  const int m0 = tm * BM, n0 = tn * BN;
-  const int nst = ldv / kBK;
-
-  uint32_t offA[CA], offB[CA];
-#pragma unroll
-  for (int j = 0; j < CA; ++j) {
-    int row, c;
-    mn_dma_target<BM>((wave * CA + j) * 64 + lane, row, c);
-    offA[j] = group_voffset(m0 + 8 * c < d ? uint32_t(row * d + m0 + 8 * c) * 2u : kOOB, j);
-    km_dma_target((wave * CA + j) * 64 + lane, row, c);
-    offB[j] = group_voffset(uint32_t((n0 + row) * ldv + 8 * c) * 2u, j);
-  }
-  const uint32_t bytesW = uint32_t(V) * uint32_t(d) * 2u;
-  const uint32_t bytesZ = uint32_t(N) * uint32_t(ldv) * 2u;
-  i32x4_t rA, rB;
-  auto prepare = [&](int st) {
-    const bool live = st < nst;
-    const int k0 = live ? st * kBK : 0;
-    const uint32_t wskip = uint32_t(k0) * uint32_t(d) * 2u;
-    rA = make_rsrc_grouped(W + int64_t(k0) * d, live && wskip < bytesW ? bytesW - wskip : 0u);
-    rB = make_rsrc_grouped(dz + k0, live ? bytesZ - 2u * uint32_t(k0) : 0u);
-  };
-  const uint32_t ldsA = lds_addr(As), ldsB = lds_addr(Bs);
-  auto issue = [&](int st, int p) {
-    const int j = p % CA;
-    const uint32_t dst = (st % STAGES) * (kBK * BM * 2) + wave * CA * 1024;
-    if (p < CA)
-      dma16_group(j, rA, offA[j], ldsA + dst);
-    else
-      dma16_group(j, rB, offB[j], ldsB + dst);
-  };
-  f32x4 acc[MB][NB];
-  gemm_mainloop<MB, NB, false, true, BM, 0, PER_STAGE, STAGES, kLmBwdRowsAfter>(
-      As, Bs, nst, wm * 128, wn * NB * 16, lane, acc, prepare, issue, [](int) {}, [](int, const u32x4(&)[NB]) {});
-  store_tile_rows<BM, MB, NB, NW>(acc, reinterpret_cast<char*>(&As[0][0]), reinterpret_cast<char*>(&Bs[0][0]), wm, wn,
-                                  tid, lane, dH, d, n0, N, m0, d);
+  wt_gemm<0, BM, BN, KS>(dz, ldv, W, V, d, N, nullptr, dH);
 }
 
 // ---------------------------------------------------------------- launchers
@@ -403,8 +355,24 @@ hipError_t launch_distill_bwd(const uint16_t* W, int N, int d, int V, const floa
                      wtok, N, V, ldv, dz);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  const int tiles = ((d + 255) / 256) * ((N + 255) / 256);
-  hipLaunchKernelGGL(lmhead_bwd_kernel, dim3(unsigned(tiles)), dim3(64 * kLmWaves), 0, s, dz, ldv, W, N, d, V, dH);
+  // The tile with the fewest estimated rounds of 256 blocks times the time per
+  // K slice (cold head and dz: 0.72 us for 256 x 256, 0.60 for 256 x 128, 0.37
+  // for 128 x 128, measured at V = 32000, d = 4096): N = 4096 keeps 256 x 256
+  // (0.93 ms against 1.18 and 1.56), N = 2048 takes 256 x 128 (0.60 ms against
+  // 0.72 and 0.73), N <= 1024 128 x 128 (0.37 ms against 0.70 and 0.51).
+  auto blocks = [&](int bm, int bn) { return int64_t((d + bm - 1) / bm) * ((N + bn - 1) / bn); };
+  const int64_t big = rounds_ns(blocks(256, 256), 720), half = rounds_ns(blocks(256, 128), 600),
+                mid = rounds_ns(blocks(128, 128), 370);
+#define GM_LM_BWD(BM, BN, KS)                                                                                \
+  hipLaunchKernelGGL((lmhead_bwd_kernel<BM, BN, KS>), dim3(unsigned(blocks(BM, BN))), dim3(64 * kLmWaves), 0, s, dz, \
+                     ldv, W, N, d, V, dH)
+  if (mid < half && mid < big)
+    GM_LM_BWD(128, 128, 2);
+  else if (half < big)
+    GM_LM_BWD(256, 128, 2);
+  else
+    GM_LM_BWD(256, 256, 1);
+#undef GM_LM_BWD
   return hipGetLastError();
 }
 

@@ -31,6 +31,16 @@ hipError_t launch_gemv_packed(const uint16_t* X, const uint16_t* Wp, const int* 
                               const int* rowptr, int T, int d_in, int d_out, int g, uint16_t* Y, hipStream_t s);
 int gemv_max_groups_per_row();
 
+// Estimated time of a GEMM launch whose blocks (one per CU) take block_ns each:
+// whole rounds of 256 blocks, and a last round that is partly empty at half a
+// round plus half its fill (its blocks run faster alone); less than one round
+// costs a whole one.
+inline int64_t rounds_ns(int64_t blocks, int64_t block_ns) {
+  const int64_t full = blocks / 256, rest = blocks % 256;
+  if (full == 0) return block_ns;
+  return full * block_ns + (rest ? block_ns / 2 + block_ns * rest / 512 : 0);
+}
+
 // Output tiles of the forward GEMM, rows of Y's columns (o) x tokens; the two
 // 128-token tiles split K over two wave groups inside the block.
 enum class FwdTile { k256x256, k256x128, k128x128 };
