@@ -35,6 +35,7 @@
 #include "gm_launch.h"
 #include "gm_lists.h"
 #include "gm_rows.h"
+#include "gm_wt.h"
 
 namespace gm {
 
@@ -46,12 +47,11 @@ constexpr int kDgateWaves = 8;
 constexpr int kDxWaves = 8;
 // dX: 8 waves for tiles of 128 and 256 rows; the 64-row tile keeps 4 (its W
 // slice is four copies, one per wave).
-constexpr int dx_waves(int bm) { return bm >= 128 ? kDxWaves : 4; }
+constexpr int dx_waves(int bm, int ks) { return bm >= 128 || ks > 1 ? kDxWaves : 4; }
 
 // LDS pipeline depth (K slices of kBK) per GEMM; the forward also keeps the
 // tile's kept bits in LDS.
 constexpr int kStagesDgate = 4;
-constexpr int kStagesDx = 4;
 
 // MFMA rows of a wave tile issued after each slice's barrier (the K-loop's RA):
 // four for the forward and dgate (2.5-5 % faster than one), one for dX (level).
@@ -700,25 +700,37 @@ __global__ __launch_bounds__(256) void zero_f32_kernel(float* __restrict__ p, in
 // (groups of 16 or 32 columns) a list column holds NSUB groups and lists
 // every row that keeps one of them; each entry carries its kept bits, and the
 // 16-byte chunks of W in a pruned group are zero-filled instead of read.
-template <int BM, int NSUB>
-__global__ __launch_bounds__(64 * dx_waves(BM)) void dx_kernel(const uint16_t* __restrict__ dYt, int ldt,
+//
+// KS = 2: two wave groups split the column's slices (contiguous shares, the
+// last padded with zero slices) over their own rings and add their tiles in
+// LDS, for launches with too few 256 x 256 tiles to fill the chip.
+template <int BM, int BN, int KS, int NSUB>
+__global__ __launch_bounds__(64 * dx_waves(BM, KS)) void dx_kernel(const uint16_t* __restrict__ dYt, int ldt,
                                                  const uint16_t* __restrict__ W, const int* __restrict__ colcount,
                                                  const int* __restrict__ rows, const float* __restrict__ scales,
                                                  const int* __restrict__ subbits, const int* __restrict__ colsoft,
                                                  int T, int d_in, int d_out, int lc, uint16_t* __restrict__ dX) {
-  constexpr int NW = dx_waves(BM), WN = NW / 2;  // waves per block; wave grid 2 (i) x WN (t)
-  constexpr int BN = 256, MB = BM / 32, NB = BN / WN / 16;
-  constexpr int KR = kBK / NW;               // k-rows of a slice gathered by one wave
-  constexpr int NA = BM / 16 / NW;           // A DMA instructions per wave per slice
-  constexpr int NBC = BN / 16 / NW;          // B DMA instructions per wave per slice
+  constexpr int NW = dx_waves(BM, KS), NG = NW / KS, WN = NG / 2;  // waves per block, per K group; wave grid 2 (i) x WN (t)
+  constexpr int MB = BM / 32, NB = BN / WN / 16;
+  constexpr int KR = kBK / NG;               // k-rows of a slice gathered by one wave
+  constexpr int NA = BM / 16 / NG;           // A DMA instructions per wave per slice
+  constexpr int NBC = BN / 16 / NG;          // B DMA instructions per wave per slice
   constexpr int PER_STAGE = NA + NBC;
-  constexpr int STAGES = kStagesDx;
-  __shared__ u32x4 As[STAGES][kBK * BM / 8];
-  __shared__ u32x4 Bs[STAGES][kBK * BN / 8];
+  constexpr int STAGES = KS * (BM + BN) > 512 ? 3 : 4;
+  constexpr int HC = BM == 256 ? MB / 4 : MB / 2;
+  static_assert(KS == 1 || KS * STAGES * (BM + BN) * 64 >= NW * HC * NB * 1024 + 2 * BM * BN, "LDS");
+  static_assert(KR * NSUB <= 64, "one lane per selector of a wave's rows");
+  __shared__ u32x4 smem[KS * STAGES * (BM + BN) * 4];  // the W rings, then the dY^T rings; afterwards the output tile
+  // (the 64 x 256 tile's ring is half a CU's LDS: its soft selectors come from memory)
+  constexpr bool MS = BM > 64 || KS > 1;
+  __shared__ float s_msoft[MS ? STAGES : 1][MS ? 64 * NW : 1];
 
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int wm = wave / WN, wn = wave % WN;
+  const int kg = wave / NG, wg = wave % NG;  // K group, wave within it
+  const int wm = wg / WN, wn = wg % WN;
+  u32x4(*As)[kBK * BM / 8] = reinterpret_cast<u32x4(*)[kBK * BM / 8]>(smem) + kg * STAGES;
+  u32x4(*Bs)[kBK * BN / 8] = reinterpret_cast<u32x4(*)[kBK * BN / 8]>(smem + KS * STAGES * BM * 4) + kg * STAGES;
   const int tiles_m = d_in / BM, tiles_n = (T + BN - 1) / BN;
   int tm, tn;
   tile_coords(gridDim.x, tiles_m, tiles_n, tm, tn);
@@ -729,14 +741,15 @@ __global__ __launch_bounds__(64 * dx_waves(BM)) void dx_kernel(const uint16_t* _
   const int* __restrict__ rl = rows + int64_t(v) * d_out;
   const int* __restrict__ bl = subbits + int64_t(v) * d_out;
   const float* __restrict__ sl = scales + int64_t(v) * d_out * NSUB;
-  const int nst = (kv + kBK - 1) / kBK;
+  const int all = (kv + kBK - 1) / kBK, nst = (all + KS - 1) / KS;
+  const int s0 = kg * nst;            // this group's slices: [s0, s0 + nst), those from `all` on zeros
   constexpr int CPS = BM / 8 / NSUB;  // 16-byte chunks per group along i (NSUB > 1)
 
-  // Slice st uses k-rows st*32 + r; this wave gathers rows r = KR wave .. KR wave + KR - 1,
+  // Slice st uses k-rows (s0 + st)*32 + r; this wave gathers rows r = KR wg .. KR wg + KR - 1,
   // whose list entries are read with scalar loads one slice ahead.
   int idx[KR], kbits[NSUB > 1 ? KR : 1];
-  auto load_idx = [&](int st) {  // st <= nst: at most 31 + 32 entries past the column's end
-    const int base = st * kBK + wave * KR;
+  auto load_idx = [&](int st) {  // at most 31 + 32 entries past the column's end
+    const int base = min(s0 + st, all) * kBK + wg * KR;
 #pragma unroll
     for (int q = 0; q < KR; ++q) {
       idx[q] = rl[base + q];  // uniform: scalar loads
@@ -750,80 +763,147 @@ __global__ __launch_bounds__(64 * dx_waves(BM)) void dx_kernel(const uint16_t* _
   // through readfirstlane keeps the compiler from turning the selects into a
   // per-lane indexed load from a stack copy of the array (for two it emits
   // one select, and the extra moves would only cost VALU issue slots).
-  auto pick_in = [&](const int* a, int j, auto rpi_c, int u) {
+  auto pick = [&](const auto* a, int j, auto rpi_c, int u) {
     constexpr int rpi = decltype(rpi_c)::value;
     auto entry = [&](int q) { return rpi > 2 ? __builtin_amdgcn_readfirstlane(a[j * rpi + q]) : a[j * rpi + q]; };
-    int o = entry(0);
+    auto o = entry(0);
 #pragma unroll
     for (int q = 1; q < rpi; ++q) o = u == q ? entry(q) : o;
-    return o;
+    return uint32_t(o);
   };
-  auto pick = [&](int j, auto rpi_c, int u) { return pick_in(idx, j, rpi_c, u); };
   constexpr std::integral_constant<int, 512 / BM> RPI_A{};
   constexpr std::integral_constant<int, 512 / BN> RPI_B{};
   const i32x4_t rA = make_rsrc_grouped(W + m0, (uint32_t(d_out) * uint32_t(d_in) - uint32_t(m0)) * 2u);
   const i32x4_t rB = make_rsrc_grouped(dYt + n0, (uint32_t(d_out) * uint32_t(ldt) - uint32_t(n0)) * 2u);
-  uint32_t offA[NA], offB[NBC];  // this slice's per-lane offsets (rows past the list read zeros)
+  // Offsets of this lane's chunks within their rows; the row offsets are scalar
+  // (bit 31: past the list's end, and dY^T columns past the matrix: zeros).
+  uint32_t colA[NA], colB[NBC], pastB[NBC];
+#pragma unroll
+  for (int j = 0; j < NA; ++j) {
+    int row, c;
+    mn_dma_target<BM>((wg * NA + j) * 64 + lane, row, c);
+    colA[j] = group_voffset(uint32_t(16 * c), j);
+  }
+#pragma unroll
+  for (int j = 0; j < NBC; ++j) {
+    int row, c;
+    mn_dma_target<BN>((wg * NBC + j) * 64 + lane, row, c);
+    colB[j] = group_voffset(uint32_t(16 * c), j);
+    pastB[j] = uint32_t(n0 + 8 * c >= ldt) << 31;
+  }
+  uint32_t offA[NA], offB[NBC];  // this slice's per-lane offsets
   auto prepare = [&](int st) {
-    const int k0 = st * kBK;
+    if constexpr (KS == 1) {
+      const int k0 = st * kBK;
+#pragma unroll
+      for (int j = 0; j < NA; ++j) {
+        int row, c;
+        mn_dma_target<BM>((wg * NA + j) * 64 + lane, row, c);
+        bool dead = k0 + row >= kv;
+        if constexpr (NSUB > 1) dead |= ((pick(kbits, j, RPI_A, lane / (BM / 8)) >> (c / CPS)) & 1) == 0;
+        offA[j] = group_voffset(uint32_t(pick(idx, j, RPI_A, lane / (BM / 8)) * d_in + 8 * c) * 2u | uint32_t(dead) << 31, j);
+      }
+#pragma unroll
+      for (int j = 0; j < NBC; ++j) {
+        int row, c;
+        mn_dma_target<BN>((wg * NBC + j) * 64 + lane, row, c);
+        offB[j] = group_voffset(uint32_t(pick(idx, j, RPI_B, lane / (BN / 8)) * ldt + 8 * c) * 2u |
+                                uint32_t(k0 + row >= kv || n0 + 8 * c >= ldt) << 31, j);
+      }
+      load_idx(st + 1);
+      return;
+    }
+    const int k0 = (s0 + st) * kBK + wg * KR;
+    uint32_t rowA[KR], rowB[KR];
+#pragma unroll
+    for (int q = 0; q < KR; ++q) {
+      rowA[q] = k0 + q < kv ? uint32_t(idx[q]) * uint32_t(d_in) * 2u : kOOB;
+      rowB[q] = k0 + q < kv ? uint32_t(idx[q]) * uint32_t(ldt) * 2u : kOOB;
+    }
 #pragma unroll
     for (int j = 0; j < NA; ++j) {
-      int row, c;
-      mn_dma_target<BM>((wave * NA + j) * 64 + lane, row, c);
-      const int o = pick(j, RPI_A, lane / (BM / 8));
-      bool dead = k0 + row >= kv;
-      if constexpr (NSUB > 1) dead |= ((pick_in(kbits, j, RPI_A, lane / (BM / 8)) >> (c / CPS)) & 1) == 0;
-      offA[j] = group_voffset(uint32_t(o * d_in + 8 * c) * 2u | uint32_t(dead) << 31, j);
+      offA[j] = pick(rowA, j, RPI_A, lane / (BM / 8)) + colA[j];
+      if constexpr (NSUB > 1) {
+        int row, c;
+        mn_dma_target<BM>((wg * NA + j) * 64 + lane, row, c);
+        offA[j] |= ((~pick(kbits, j, RPI_A, lane / (BM / 8)) >> (c / CPS)) & 1u) << 31;
+      }
     }
 #pragma unroll
-    for (int j = 0; j < NBC; ++j) {
-      int row, c;
-      mn_dma_target<BN>((wave * NBC + j) * 64 + lane, row, c);
-      const int o = pick(j, RPI_B, lane / (BN / 8));
-      offB[j] = group_voffset(uint32_t(o * ldt + 8 * c) * 2u | uint32_t(k0 + row >= kv || n0 + 8 * c >= ldt) << 31, j);
-    }
-    load_idx(min(st + 1, nst));
+    for (int j = 0; j < NBC; ++j) offB[j] = (pick(rowB, j, RPI_B, lane / (BN / 8)) + colB[j]) | pastB[j];
+    load_idx(st + 1);
   };
-  const uint32_t ldsA = lds_addr(As), ldsB = lds_addr(Bs);
+  const uint32_t ldsA = lds_addr(smem) + uint32_t(kg) * (STAGES * BM * 64);
+  const uint32_t ldsB = lds_addr(smem) + uint32_t(KS * STAGES * BM * 64) + uint32_t(kg) * (STAGES * BN * 64);
   auto issue = [&](int st, int p) {  // copies 0 .. NA-1: W tile, NA .. NA+NBC-1: dY^T tile
     if (p < NA)
-      dma16_group(p, rA, offA[p], ldsA + (st % STAGES) * (kBK * BM * 2) + wave * NA * 1024);
+      dma16_group(p, rA, offA[p], ldsA + (st % STAGES) * (kBK * BM * 2) + wg * NA * 1024);
     else
-      dma16_group(p - NA, rB, offB[p - NA], ldsB + (st % STAGES) * (kBK * BN * 2) + wave * NBC * 1024);
+      dma16_group(p - NA, rB, offB[p - NA], ldsB + (st % STAGES) * (kBK * BN * 2) + wg * NBC * 1024);
   };
-  // Soft selectors: scale this lane's landed W chunks by the row's mask value.
+  // Soft selectors: with every slice's copies the wave also copies the
+  // selectors of its own KR list entries (a contiguous run of scales), and
+  // scales its W chunks once both landed.
+  const i32x4_t rM = make_rsrc(sl, uint32_t(kv) * uint32_t(NSUB) * 4u);
+  const uint32_t ldsM = lds_addr(s_msoft) + uint32_t(wave) * 256u;
+  auto prepare_soft = [&](int st) {
+    const uint32_t at = (uint32_t((s0 + st) * kBK + wg * KR) * uint32_t(NSUB) + uint32_t(lane)) * 4u;
+    if constexpr (MS) dma4_buf(rM, lane < KR * NSUB ? at : kOOB, ldsM + uint32_t(st % STAGES) * (64u * NW * 4u));
+    prepare(st);
+  };
   auto rescale = [&](int st) {
-    const int k0 = st * kBK;
+    const float* ms = s_msoft[MS ? st % STAGES : 0] + (MS ? 64 * wave : 0);
     u32x4* A = As[st % STAGES];
-    float m[NA];
-    u32x4 w[NA];  // the selectors and the chunks they scale, all read at once
+    constexpr int HS = NA > 2 ? 1 : NA;  // chunks scaled at once (the larger tile has fewer registers to spare)
 #pragma unroll
-    for (int j = 0; j < NA; ++j) {
-      int row, c;
-      mn_dma_target<BM>((wave * NA + j) * 64 + lane, row, c);
-      const int at = k0 + row;
-      m[j] = at < kv ? (NSUB > 1 ? sl[at * NSUB + c / CPS] : sl[at]) : 1.0f;
-      w[j] = A[(wave * NA + j) * 64 + lane];
+    for (int h = 0; h < NA; h += HS) {
+      float m[HS];
+      u32x4 w[HS];
+#pragma unroll
+      for (int j = 0; j < HS; ++j) {
+        int row, c;
+        mn_dma_target<BM>((wg * NA + h + j) * 64 + lane, row, c);
+        const int at = row * NSUB + (NSUB > 1 ? c / CPS : 0);
+        m[j] = MS ? ms[at - wg * KR * NSUB] : (s0 + st) * kBK + row < kv ? sl[(s0 + st) * kBK * NSUB + at] : 1.0f;
+        w[j] = A[(wg * NA + h + j) * 64 + lane];
+      }
+#pragma unroll
+      for (int j = 0; j < HS; ++j)
+        if (m[j] != 1.0f) A[(wg * NA + h + j) * 64 + lane] = scale_bf16x8(w[j], m[j]);
     }
-#pragma unroll
-    for (int j = 0; j < NA; ++j)
-      if (m[j] != 1.0f) A[(wave * NA + j) * 64 + lane] = scale_bf16x8(w[j], m[j]);
     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
   };
 
   // Columns whose kept selectors are all exactly 1 run a loop without the rescaling step.
   f32x4 acc[MB][NB];
   load_idx(0);
+  auto hook = [](int, const u32x4(&)[NB]) {};
   if (soft)
-    gemm_mainloop<MB, NB, false, false, BM, BN, PER_STAGE, STAGES, kDxRowsAfter>(
-        As, Bs, nst, wm * (BM / 2), wn * NB * 16, lane, acc, prepare, issue, rescale, [](int, const u32x4(&)[NB]) {});
+    gemm_mainloop<MB, NB, false, false, BM, BN, PER_STAGE, STAGES, kDxRowsAfter, MS>(
+        As, Bs, nst, wm * (BM / 2), wn * NB * 16, lane, acc, prepare_soft, issue, rescale, hook);
   else
     gemm_mainloop<MB, NB, false, false, BM, BN, PER_STAGE, STAGES, kDxRowsAfter>(
-        As, Bs, nst, wm * (BM / 2), wn * NB * 16, lane, acc, prepare, issue, [](int) {}, [](int, const u32x4(&)[NB]) {});
+        As, Bs, nst, wm * (BM / 2), wn * NB * 16, lane, acc, prepare, issue, [](int) {}, hook);
 
-  char* const hi = reinterpret_cast<char*>(&Bs[0][0]);
-  store_tile_rows<BM, MB, NB, NW>(acc, BM == 256 ? reinterpret_cast<char*>(&As[0][0]) : hi, hi, wm, wn, tid, lane, dX,
-                                  d_in, n0, T, m0, d_in);
+  char* const hi = reinterpret_cast<char*>(smem + STAGES * BM * 4);
+  if constexpr (KS == 1)
+    store_tile_rows<BM, MB, NB, NW>(acc, BM == 256 ? reinterpret_cast<char*>(smem) : hi, hi, wm, wn, tid, lane, dX,
+                                    d_in, n0, T, m0, d_in);
+  else
+    store_tile_ksum2<BM, BN, MB, NB, NW, HC>(acc, reinterpret_cast<f32x4*>(smem),
+                                             reinterpret_cast<char*>(smem) + NW * HC * NB * 1024, kg, wg, wm, wn, tid,
+                                             lane, dX, d_in, n0, T, m0, d_in);
+}
+
+// dX of small square groups over every row: a list column of 64 input columns
+// (four or two groups) keeps 94 % or 75 % of the rows at half the groups kept,
+// so gathering rows saves little, and its 64-column tiles move 1.9 times the
+// operand bytes per MFMA of a 256-column tile.
+template <int G, int BM, int BN, int KS>
+__global__ __launch_bounds__(512) void dx_dense_kernel(const uint16_t* __restrict__ dY, const uint16_t* __restrict__ W,
+                                                       const float* __restrict__ mask, int T, int d_in, int d_out,
+                                                       uint16_t* __restrict__ dX) {
+  wt_gemm<G, BM, BN, KS>(dY, d_out, W, d_out, d_in, T, mask, dX);
 }
 
 // ============================================================================ dY^T
@@ -965,28 +1045,84 @@ hipError_t launch_dx(const uint16_t* dYt, int ldt, const uint16_t* W, const int*
                      const float* scales, const int* subbits, const int* colsoft, int T, int d_in, int d_out, int g,
                      uint16_t* dX, hipStream_t s) {
   const int lc = g < 64 ? 64 : g;  // list-column width
-  int bm = lc < 256 ? lc : 256;
-  // A launch of fewer than 64 tiles (the 128-token, 1024 x 1024 linear has 4)
-  // takes tiles of 64 columns, four times as many blocks over the same lists.
-  if (g >= 64 && bm > 64 && (d_in / bm) * ((T + 255) / 256) < 64) bm = 64;
-  const int tiles = (d_in / bm) * ((T + 255) / 256);
-#define GM_DX(BM, NSUB)                                                                                        \
-  hipLaunchKernelGGL((dx_kernel<BM, NSUB>), dim3(tiles), dim3(64 * dx_waves(BM)), 0, s, dYt, ldt, W, colcount, \
-                     rows, scales, subbits, colsoft, T, d_in, d_out, lc, dX)
-  switch (g) {
-    case 16: GM_DX(64, 4); break;
-    case 32: GM_DX(64, 2); break;
-    case 64: GM_DX(64, 1); break;
-    case 128:
-      if (bm == 64) GM_DX(64, 1); else GM_DX(128, 1);
-      break;
-    case 256:
-    case 512:
-      if (bm == 64) GM_DX(64, 1); else GM_DX(256, 1);
-      break;
-    default: return hipErrorInvalidValue;
+  auto blocks = [&](int m, int n) { return int64_t(d_in / m) * ((T + n - 1) / n); };
+#define GM_DX(BM, BN, KS, NSUB)                                                                                \
+  hipLaunchKernelGGL((dx_kernel<BM, BN, KS, NSUB>), dim3(unsigned(blocks(BM, BN))), dim3(64 * dx_waves(BM, KS)), 0, \
+                     s, dYt, ldt, W, colcount, rows, scales, subbits, colsoft, T, d_in, d_out, lc, dX)
+  if (g == 16) {
+    GM_DX(64, 256, 1, 4);
+    return hipGetLastError();
+  }
+  if (g == 32) {
+    GM_DX(64, 256, 1, 2);
+    return hipGetLastError();
+  }
+  // The tile with the lowest estimated time among those that divide the list
+  // column; the slices of a column are taken as half its rows.  Us per block
+  // and round + us per 32-deep slice, fitted to LLaMA-2-7B shapes at T = 128 ..
+  // 4096, half the groups kept: 256 x 256 19 + 0.64, 256 x 128 (two K groups)
+  // 16 + 0.49, 128 x 256 14 + 0.62, 128 x 128 (two) 13 + 0.39, 64 x 128 (two)
+  // 15 + 0.29; the 64 x 256 tile runs two blocks per CU (13 + 0.78 per round of
+  // 512, 13 + 0.50 below half of one).  E.g. 4096 x 4096, 1 x 256 groups: T =
+  // 4096 67 us in 256 x 256 tiles (96 in 256 x 128), T = 2048 51 in 256 x 128 (59),
+  // T = 1024 38 in 128 x 128 (58), T = 128 32 in 64 x 128 (44 in 64 x 256); 11008
+  // rows, T = 1024 81 in 128 x 128 (128 in 256 x 256).
+  const int64_t sl = (d_out + 63) / 64;
+  enum { kBig, kHalf, kWide, kMid, kLow, kPair } tile = kLow;
+  int64_t best = rounds_ns(blocks(64, 128), 15000 + 290 * sl);
+  auto consider = [&](auto t, int64_t ns) {
+    if (ns < best) tile = t, best = ns;
+  };
+  if (lc >= 128) consider(kMid, rounds_ns(blocks(128, 128), 13000 + 390 * sl));
+  if (lc == 128) consider(kWide, rounds_ns(blocks(128, 256), 14000 + 620 * sl));
+  if (lc >= 256) consider(kHalf, rounds_ns(blocks(256, 128), 16000 + 490 * sl));
+  if (lc >= 256) consider(kBig, rounds_ns(blocks(256, 256), 19000 + 640 * sl));
+  if (lc == 64)
+    consider(kPair, blocks(64, 256) <= 256 ? 13000 + 500 * sl : rounds_ns(blocks(64, 256) / 2, 13000 + 780 * sl));
+  switch (tile) {
+    case kBig: GM_DX(256, 256, 1, 1); break;
+    case kHalf: GM_DX(256, 128, 2, 1); break;
+    case kWide: GM_DX(128, 256, 1, 1); break;
+    case kMid: GM_DX(128, 128, 2, 1); break;
+    case kLow: GM_DX(64, 128, 2, 1); break;
+    case kPair: GM_DX(64, 256, 1, 1); break;
   }
 #undef GM_DX
+  return hipGetLastError();
+}
+
+bool dx_dense_ok(int d_out, int g) { return g < 64 && d_out / g <= kWtMaskRows; }
+
+hipError_t launch_dx_dense(const uint16_t* dY, const uint16_t* W, const float* mask, int T, int d_in, int d_out, int g,
+                           uint16_t* dX, hipStream_t s) {
+  auto blocks = [&](int bm, int bn) { return int64_t((d_in + bm - 1) / bm) * ((T + bn - 1) / bn); };
+  // The tile with the lowest estimated time (us per block and round: 10 + 0.70
+  // per K slice for 256 x 256, 11 + 0.45 for 256 x 128, 7 + 0.24 for 128 x 128;
+  // 4096 x 4096, 32 x 32 groups: T = 4096 101 / 127 / 150 us, T = 2048 97 / 69 /
+  // 78, T = 512 88 / 60 / 37).
+  const int64_t slices = (d_out + 31) / 32;
+  const int64_t big = rounds_ns(blocks(256, 256), 10000 + 700 * slices),
+                half = rounds_ns(blocks(256, 128), 11000 + 450 * slices),
+                mid = rounds_ns(blocks(128, 128), 7000 + 240 * slices);
+#define GM_DENSE(G, BM, BN, KS)                                                                                  \
+  hipLaunchKernelGGL((dx_dense_kernel<G, BM, BN, KS>), dim3(unsigned(blocks(BM, BN))), dim3(512), 0, s, dY, W, mask, T, \
+                     d_in, d_out, dX)
+#define GM_DENSE_G(G)                        \
+  if (mid < half && mid < big)               \
+    GM_DENSE(G, 128, 128, 2);                \
+  else if (half < big)                       \
+    GM_DENSE(G, 256, 128, 2);                \
+  else                                       \
+    GM_DENSE(G, 256, 256, 1);
+  if (g == 16) {
+    GM_DENSE_G(16)
+  } else if (g == 32) {
+    GM_DENSE_G(32)
+  } else {
+    return hipErrorInvalidValue;
+  }
+#undef GM_DENSE_G
+#undef GM_DENSE
   return hipGetLastError();
 }
 

@@ -67,6 +67,11 @@ hipError_t launch_dx(const uint16_t* dYt, int ldt, const uint16_t* W, const int*
                      const float* scales, const int* subbits, const int* colsoft, int T, int d_in, int d_out, int g,
                      uint16_t* dX, hipStream_t s);
 
+// dX of 16 x 16 and 32 x 32 groups straight from dY and W (no column lists, no dY^T).
+bool dx_dense_ok(int d_out, int g);
+hipError_t launch_dx_dense(const uint16_t* dY, const uint16_t* W, const float* mask, int T, int d_in, int d_out, int g,
+                           uint16_t* dX, hipStream_t s);
+
 // Distillation loss (Sec. 2.4, Eq. 4) through the LM head.
 int distill_vocab_tiles(int V);
 hipError_t launch_distill_fwd(const uint16_t* Ht, const uint16_t* Hs, const uint16_t* W, const uint8_t* valid, int N,

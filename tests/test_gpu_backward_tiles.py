@@ -1,11 +1,63 @@
-"""GPU parity of the LM head's backward in each of its tiles against the fp64 oracle, at tile edges."""
+"""GPU parity of the backward GEMMs' tiles against the fp64 oracle, at tile edges: dX over column lists in its
+64- to 256-column tiles with and without two K groups, dX of 16 x 16 and 32 x 32 groups over every row, and the LM
+head's backward in each of its tiles."""
+import numpy as np
 import pytest
 
 import oracle
 import workloads
-from gpu_support import assert_close, dev_bf16, empty_bf16, empty_f32, host_f64_from_bf16, say, sync, workspace
+from gpu_support import (assert_close, dev_bf16, dev_f32, empty_bf16, empty_f32, host_bits, host_f64_from_bf16, ref_dx,
+                         say, sync, workspace)
 
 pytestmark = pytest.mark.gpu
+
+
+def _dx(case, mask, with_dgate):
+    import paper_2609_33977_amd as gm
+    T, d_in, d_out, g, go = case.T, case.d_in, case.d_out, case.g, case.g_out
+    dX = empty_bf16(T, d_in)
+    dgate = empty_f32(*mask.shape) if with_dgate else None
+    ws = workspace(gm.gm_workspace_size(gm.GM_OP_BWD, T, d_in, d_out, g, go))
+    gm.gm_masked_linear_bwd(dev_bf16(case.dY), dev_bf16(case.X), dev_bf16(case.W), dev_f32(mask), g, dX, dgate, ws,
+                            g_out=go)
+    sync()
+    return dX
+
+
+def _soften(mask, key):
+    r = workloads.gen.rng_for(key)
+    soft = np.where(mask != 0, r.uniform(0.05, 1.5, size=mask.shape), 0.0).astype(np.float32)
+    soft[mask.shape[0] // 2:, 0] = 1.0
+    return soft
+
+
+@pytest.mark.parametrize("soft", [False, True])
+@pytest.mark.parametrize("T,d_in,d_out,g,g_out", [
+    (17, 64, 8, 64, 1),         # one slice: the second K group has none
+    (130, 1024, 1032, 256, 1),  # 64 x 128 tiles of 256-wide columns, ragged tokens and rows
+    (260, 512, 512, 512, 1),
+    (1030, 2816, 520, 128, 1),  # 128 x 128 tiles
+    (2050, 4096, 264, 256, 1),  # 256 x 128 tiles
+    (2050, 4096, 264, 128, 1),  # 128 x 256 tiles
+    (300, 384, 384, 128, 128),
+    (1000, 16384, 128, 64, 64),  # 64 x 256 tiles, two blocks per CU
+    (33, 64, 32, 16, 16),       # every row: one slice, a single mask-row pair
+    (140, 320, 336, 16, 16),    # K not a multiple of 32, columns past the last tile
+    (257, 576, 96, 32, 32),
+    (1100, 4096, 160, 32, 32),  # 256 x 128 tiles
+    (4000, 4096, 64, 16, 16),   # 256 x 256 tiles
+])
+def test_dx_tiles(T, d_in, d_out, g, g_out, soft):
+    say(f"dX tiles: T={T} d_in={d_in} d_out={d_out} g={g} g_out={g_out} soft={soft}")
+    case = workloads.make_linear_case((290, T, d_in, d_out, g), T, d_in, d_out, g, None, g_out=g_out)
+    mask = case.mask.astype(np.float32).copy()
+    mask[:, -1] = 0.0  # a pruned column
+    if soft:
+        mask = _soften(mask, 291)
+    ref, b = ref_dx(oracle.from_bf16(case.dY), oracle.from_bf16(case.W), mask, g, g_out)
+    dX = _dx(case, mask, True)
+    assert_close("dX", host_f64_from_bf16(dX), ref, bound=b)
+    assert np.array_equal(host_bits(dX), host_bits(_dx(case, mask, False))), "dX differs without dgate beside it"
 
 
 @pytest.mark.parametrize("N,d,V", [
