@@ -28,10 +28,9 @@ namespace gm {
 constexpr int kLmWaves = 8;
 constexpr int kLmTokens = 128;  // tokens of each pass per forward tile
 constexpr int kLmStats = 5;     // m_T, s_T, m_S, s_S, c per token and vocabulary tile
-// MFMA rows of a wave tile issued after each slice's barrier in the K-loop:
-// four measured 1.6 % faster for the backward GEMM and 0.6 % slower for the
-// forward one (whose epilogue dominates), so the forward keeps one.
-constexpr int kLmFwdRowsAfter = 1;
+// MFMA rows of a wave tile issued after each slice's barrier in the forward's
+// K-loop: one, two and four measured level to 1 %.
+constexpr int kLmFwdRowsAfter = 2;
 
 // (m, s) <- merge of two (max, sum of exp(x - max)) summaries; an empty one has m = -inf, s = 0.
 __device__ __forceinline__ void lse_merge(float& m, float& s, float m2, float s2) {
@@ -51,13 +50,28 @@ __device__ __forceinline__ void lse_merge_c(float& m, float& s, float& c, float 
   m = mx;
 }
 
+// exp(x) for x <= 0 (or -inf, NaN): exp2 of x log2(e) with the product's
+// rounding error carried to first order, as accurate as expf where the result
+// is normal and without its range reduction and overflow handling; results
+// below 2^-126 are 0.
+__device__ __forceinline__ float exp_nonpos(float x) {
+  constexpr float kLog2e = 1.44269502e+00f, kLog2eLo = 1.92596303e-08f, kLn2 = 6.93147182e-01f;  // hi + lo = log2(e)
+  const float h = x * kLog2e;
+  const float l = __builtin_fmaf(x, kLog2eLo, __builtin_fmaf(x, kLog2e, -h));
+  const float e = __builtin_amdgcn_exp2f(h);
+  return __builtin_fmaf(e, x < -200.0f ? 0.0f : l * kLn2, e);
+}
+
 // ---------------------------------------------------------------- forward GEMM
 
 // Tile: 256 vocabulary rows (M, K-major W rows) x 256 columns (N): columns
 // 0..127 are tokens t0..t0+127 of the teacher, 128..255 the same tokens of the
 // student.  Waves 2 (M) x 4 (N): waves with wn < 2 hold teacher logits, the
 // others the student logits of the same tokens and rows.  part holds the
-// statistics as [N][tiles of V][kLmStats].
+// statistics as [N][tiles of V][kLmStats].  Per tile at d = 4096 the K-loop
+// takes about 115 us and everything after it 12 (N = 2048, V = 32000: 0.91 ms of
+// 0.99); with the reduction on the student waves alone and the logits stored
+// in 64-byte pieces straight from the fragments it was 1.14 ms.
 __global__ __launch_bounds__(64 * kLmWaves) void lmhead_fwd_kernel(const uint16_t* __restrict__ Ht,
                                                                   const uint16_t* __restrict__ Hs,
                                                                   const uint16_t* __restrict__ W, int N, int d,
@@ -67,7 +81,7 @@ __global__ __launch_bounds__(64 * kLmWaves) void lmhead_fwd_kernel(const uint16_
   constexpr int BM = 256, BN = 2 * kLmTokens, MB = 8, NB = BN / WN / 16;
   constexpr int PER_STAGE = 32 / NW, CA = PER_STAGE / 2, STAGES = 4;
   __shared__ u32x4 smem[2 * STAGES * BM * 4];  // the A and B rings; afterwards the teacher logits
-  __shared__ float s_half[2][kLmTokens][kLmStats];
+  __shared__ float s_part[4][kLmTokens][kLmStats];
   u32x4(*As)[BM * 4] = reinterpret_cast<u32x4(*)[BM * 4]>(smem);
   u32x4(*Bs)[BN * 4] = reinterpret_cast<u32x4(*)[BN * 4]>(smem + STAGES * BM * 4);
 
@@ -118,59 +132,57 @@ __global__ __launch_bounds__(64 * kLmWaves) void lmhead_fwd_kernel(const uint16_
   auto vrow = [&](int mb) { return v0 + wm * 128 + mb * 16 + 4 * q; };
   auto tcol = [&](int nb) { return (wn % (WN / 2)) * 64 + nb * 16 + r; };  // token within the tile
 
-  // 1. Both passes' logits to HBM (fp32, [N, V]; V is a multiple of 4, so a
-  //    row quad is entirely inside or outside the vocabulary).
-  float* zout = teacher ? zt : zs;
+  // 1. Teacher and student waves that hold the same rows and tokens swap halves
+  //    of them through the freed ring (fragment rows [0, MB/2) go to the teacher
+  //    wave, the rest to the student wave), so that all eight waves reduce.
+  f32x4* zl = reinterpret_cast<f32x4*>(smem);
+  constexpr int HB = MB / 2;
+  const int pair = wm * 2 + (wn % 2);
+  auto slot = [&](int side, int mb, int nb) { return (((pair * 2 + side) * HB + mb) * NB + nb) * 64 + lane; };
+  __syncthreads();  // every wave has left the K-loop (its copies drained)
 #pragma unroll
-  for (int mb = 0; mb < MB; ++mb)
+  for (int mb = 0; mb < HB; ++mb)
 #pragma unroll
     for (int nb = 0; nb < NB; ++nb) {
-      const int v = vrow(mb), t = t0 + tcol(nb);
-      if (t < N && v < V) *reinterpret_cast<f32x4*>(zout + int64_t(t) * V + v) = acc[mb][nb];
+      if (teacher) zl[slot(0, mb, nb)] = acc[HB + mb][nb];
+      else zl[slot(1, mb, nb)] = acc[mb][nb];
     }
-
-  // 2. The teacher waves hand their logits to the student waves holding the
-  //    same rows and tokens (slot by wave row, column pair, fragment and lane).
-  f32x4* zl = reinterpret_cast<f32x4*>(smem);
-  auto slot = [&](int mb, int nb) { return (((wm * 2 + (wn % 2)) * MB + mb) * NB + nb) * 64 + lane; };
-  __syncthreads();  // every wave has left the K-loop (its copies drained)
-  if (teacher) {
-#pragma unroll
-    for (int mb = 0; mb < MB; ++mb)
-#pragma unroll
-      for (int nb = 0; nb < NB; ++nb) zl[slot(mb, nb)] = acc[mb][nb];
-  }
   __syncthreads();
 
-  // 3. The student waves reduce each token over their 128 rows: per lane over
-  //    32 rows, then over the four lane groups; the two wave rows meet in LDS.
-  if (!teacher) {
+  // 2. Each wave reduces its tokens over its 64 rows: per lane over 16 rows,
+  //    then over the four lane groups; the four parts of a token meet in LDS.
+  //    Rows past the vocabulary (the last tile only) are left out.
+  auto reduce = [&](auto side_c, auto ragged_c) {
+    constexpr int SIDE = decltype(side_c)::value;  // 0: teacher wave, rows of fragments [0, HB)
+    constexpr bool RAGGED = decltype(ragged_c)::value;
+    auto in = [&](int mb, int k) { return !RAGGED || vrow(SIDE * HB + mb) + k < V; };
 #pragma unroll
     for (int nb = 0; nb < NB; ++nb) {
+      f32x4 zt4[HB], zs4[HB];
       float mt = -INFINITY, ms = -INFINITY;
 #pragma unroll
-      for (int mb = 0; mb < MB; ++mb) {
-        const f32x4 ztv = zl[slot(mb, nb)];
+      for (int mb = 0; mb < HB; ++mb) {
+        const f32x4 other = zl[slot(1 - SIDE, mb, nb)];
+        zt4[mb] = SIDE == 0 ? acc[mb][nb] : other;
+        zs4[mb] = SIDE == 0 ? other : acc[HB + mb][nb];
 #pragma unroll
         for (int k = 0; k < 4; ++k)
-          if (vrow(mb) + k < V) {
-            mt = fmaxf(mt, ztv[k]);
-            ms = fmaxf(ms, acc[mb][nb][k]);
+          if (in(mb, k)) {
+            mt = fmaxf(mt, zt4[mb][k]);
+            ms = fmaxf(ms, zs4[mb][k]);
           }
       }
       float st = 0.0f, ss = 0.0f, c = 0.0f;
 #pragma unroll
-      for (int mb = 0; mb < MB; ++mb) {
-        const f32x4 ztv = zl[slot(mb, nb)];
+      for (int mb = 0; mb < HB; ++mb)
 #pragma unroll
         for (int k = 0; k < 4; ++k)
-          if (vrow(mb) + k < V) {
-            const float e = expf(ztv[k] - mt);
+          if (in(mb, k)) {
+            const float e = exp_nonpos(zt4[mb][k] - mt);
             st += e;
-            c += e * acc[mb][nb][k];
-            ss += expf(acc[mb][nb][k] - ms);
+            c += e * zs4[mb][k];
+            ss += exp_nonpos(zs4[mb][k] - ms);
           }
-      }
 #pragma unroll
       for (int x = 16; x <= 32; x <<= 1) {
         const float mt2 = __shfl_xor(mt, x), st2 = __shfl_xor(st, x), c2 = __shfl_xor(c, x);
@@ -179,7 +191,7 @@ __global__ __launch_bounds__(64 * kLmWaves) void lmhead_fwd_kernel(const uint16_
         lse_merge(ms, ss, ms2, ss2);
       }
       if (q == 0) {
-        float* h = s_half[wm][tcol(nb)];
+        float* h = s_part[wm * 2 + SIDE][tcol(nb)];
         h[0] = mt;
         h[1] = st;
         h[2] = ms;
@@ -187,14 +199,25 @@ __global__ __launch_bounds__(64 * kLmWaves) void lmhead_fwd_kernel(const uint16_
         h[4] = c;
       }
     }
+  };
+  const bool ragged = v0 + BM > V;  // uniform
+  if (teacher) {
+    if (ragged) reduce(std::integral_constant<int, 0>{}, std::true_type{});
+    else reduce(std::integral_constant<int, 0>{}, std::false_type{});
+  } else {
+    if (ragged) reduce(std::integral_constant<int, 1>{}, std::true_type{});
+    else reduce(std::integral_constant<int, 1>{}, std::false_type{});
   }
   __syncthreads();
   if (tid < kLmTokens && t0 + tid < N) {
-    const float* a = s_half[0][tid];
-    const float* b = s_half[1][tid];
+    const float* a = s_part[0][tid];
     float mt = a[0], st = a[1], ms = a[2], ss = a[3], c = a[4];
-    lse_merge_c(mt, st, c, b[0], b[1], b[4]);
-    lse_merge(ms, ss, b[2], b[3]);
+#pragma unroll
+    for (int h = 1; h < 4; ++h) {
+      const float* b = s_part[h][tid];
+      lse_merge_c(mt, st, c, b[0], b[1], b[4]);
+      lse_merge(ms, ss, b[2], b[3]);
+    }
     float* p = part + (int64_t(t0 + tid) * tiles_m + tm) * kLmStats;
     p[0] = mt;
     p[1] = st;
@@ -202,6 +225,32 @@ __global__ __launch_bounds__(64 * kLmWaves) void lmhead_fwd_kernel(const uint16_
     p[3] = ss;
     p[4] = c;
   }
+
+  // 3. Both passes' logits to HBM (fp32, [N, V]), one pass after the other: the
+  //    tile goes through LDS as 128 token rows of 1 KiB (16-byte chunk c of row
+  //    n at slot c ^ (n mod 8)) and out as whole rows, nontemporal (they are
+  //    read once, after more data than the caches hold).
+  auto store_pass = [&](bool mine, float* __restrict__ zout) {
+    if (mine) {
+#pragma unroll
+      for (int mb = 0; mb < MB; ++mb)
+#pragma unroll
+        for (int nb = 0; nb < NB; ++nb) {
+          const int n = tcol(nb), c = wm * 32 + mb * 4 + q;
+          zl[n * 64 + (c ^ (n & 7))] = acc[mb][nb];
+        }
+    }
+    __syncthreads();
+#pragma unroll 4
+    for (int k = 0; k < kLmTokens / NW; ++k) {
+      const int n = k * NW + wave, v = v0 + 4 * lane;  // V is a multiple of 4
+      const f32x4 x = zl[n * 64 + (lane ^ (n & 7))];
+      if (t0 + n < N && v < V) __builtin_nontemporal_store(x, reinterpret_cast<f32x4*>(zout + int64_t(t0 + n) * V + v));
+    }
+  };
+  store_pass(teacher, zt);
+  __syncthreads();  // the rows are read before the student's replace them
+  store_pass(!teacher, zs);
 }
 
 // ---------------------------------------------------------------- per token
