@@ -49,10 +49,6 @@ constexpr int kDxWaves = 8;
 // slice is four copies, one per wave).
 constexpr int dx_waves(int bm, int ks) { return bm >= 128 || ks > 1 ? kDxWaves : 4; }
 
-// LDS pipeline depth (K slices of kBK) per GEMM; the forward also keeps the
-// tile's kept bits in LDS.
-constexpr int kStagesDgate = 4;
-
 // MFMA rows of a wave tile issued after each slice's barrier (the K-loop's RA):
 // four for the forward and dgate (2.5-5 % faster than one), one for dX (level).
 constexpr int kFwdRowsAfter = 4, kDgateRowsAfter = 4, kDxRowsAfter = 1;
@@ -465,10 +461,17 @@ __global__ __launch_bounds__(256) void fwd_reduce_kernel(const float* __restrict
 
 // ============================================================================ dgate
 
-// C[i, o] = sum_t X[t, i] dY[t, o], tile 256 (i) x 256 (o); waves 2 (i) x 4 (o).
+// C[i, o] = sum_t X[t, i] dY[t, o], tile 256 (i) x BN (o); waves 2 (i) x WN (o).
 // The epilogue forms dgate[o, v] = sum_{i in v} W[o, i] C[i, o].  For g = 512 a
 // group spans two tiles, each adding its half onto a zeroed dgate (two
 // addends onto zero: the same sum whichever lands first).
+//
+// KS = 2: two wave groups split the tokens' slices (contiguous shares, the
+// last padded with zero slices) over their own rings, for launches with too
+// few 256 x 256 tiles to fill the chip.  The group sums are linear in C, so
+// each wave group weights and sums its own part of C, and only the group sums
+// are added, in LDS: no accumulators are exchanged (dgate of a 1024 x 1024
+// linear at T = 2048: 49 us in 16 256 x 256 tiles, 26 us in 64 256 x 64 tiles).
 //
 // Blocks past the tiles (when the dX GEMM follows) build the mask's column
 // lists, one col_lists_unit each: they start as the first tiles finish, on
@@ -481,22 +484,22 @@ struct ListArgs {
   float* scales;
 };
 
-template <int G, int GO>
-__global__ __launch_bounds__(64 * kDgateWaves) void dgate_kernel(const uint16_t* __restrict__ dY, const uint16_t* __restrict__ X,
-                                                    const uint16_t* __restrict__ W, int T, int d_in, int d_out,
-                                                    float* __restrict__ dgate, uint16_t* __restrict__ dYt, int ldt,
-                                                    ListArgs la) {
-  constexpr int NW = kDgateWaves, WN = NW / 2;  // waves per block; wave grid 2 (i) x WN (o)
-  constexpr int BM = 256, BN = 256, MB = 8, NB = BN / WN / 16;
-  constexpr int PER_STAGE = 32 / NW;
-  constexpr int CA = PER_STAGE / 2;  // copies of the X tile per wave (the rest: dY tile)
-  constexpr int STAGES = kStagesDgate;
-  __shared__ u32x4 As[STAGES][kBK * BM / 8];
-  __shared__ u32x4 Bs[STAGES][kBK * BN / 8];
+template <int G, int GO, int BN, int KS>
+__device__ __forceinline__ void dgate_tile(const uint16_t* __restrict__ dY, const uint16_t* __restrict__ X,
+                                           const uint16_t* __restrict__ W, int T, int d_in, int d_out,
+                                           float* __restrict__ dgate, uint16_t* __restrict__ dYt, int ldt,
+                                           const ListArgs& la) {
+  constexpr int NW = kDgateWaves, NG = NW / KS, WN = NG / 2;  // waves per block, per K group; wave grid 2 (i) x WN (o)
+  constexpr int BM = 256, MB = 8, NB = BN / WN / 16;
+  constexpr int CA = BM / 16 / NG, CB = BN / 16 / NG;  // copies of the X tile, of the dY tile per wave per slice
+  constexpr int PER_STAGE = CA + CB;
+  constexpr int STAGES = KS * (BM + BN) > 512 ? 3 : 4;
+  __shared__ u32x4 smem[KS * STAGES * (BM + BN) * 4];  // the X rings, then the dY rings; afterwards the group sums
 
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int wm = wave / WN, wn = wave % WN;
+  const int kg = wave / NG, wg = wave % NG;  // K group, wave within it
+  const int wm = wg / WN, wn = wg % WN;
   const int G_in = d_in / G;
   const int tiles_m = (d_in + BM - 1) / BM, tiles_n = (d_out + BN - 1) / BN, tiles = tiles_m * tiles_n;
   if (int(blockIdx.x) >= tiles) {
@@ -504,69 +507,86 @@ __global__ __launch_bounds__(64 * kDgateWaves) void dgate_kernel(const uint16_t*
                             la.colsoft, la.rows, la.scales, la.subbits);
     return;
   }
+  u32x4(*As)[kBK * BM / 8] = reinterpret_cast<u32x4(*)[kBK * BM / 8]>(smem) + kg * STAGES;
+  u32x4(*Bs)[kBK * BN / 8] = reinterpret_cast<u32x4(*)[kBK * BN / 8]>(smem + KS * STAGES * BM * 4) + kg * STAGES;
   int tm, tn;
   tile_coords(int(blockIdx.x), tiles, tiles_m, tiles_n, tm, tn);
   const int m0 = tm * BM, n0 = tn * BN;
-  const int nst = (T + kBK - 1) / kBK;
+  const int all = (T + kBK - 1) / kBK, nst = (all + KS - 1) / KS;
+  const int s0 = kg * nst;  // this group's slices: [s0, s0 + nst), those from `all` on zeros
 
   // Byte offsets of this lane's DMA chunks within a K slice (columns past the
   // matrix read zeros; rows past T fall outside the slice's range).
-  uint32_t offA[CA], offB[CA];
+  uint32_t offA[CA], offB[CB];
 #pragma unroll
   for (int j = 0; j < CA; ++j) {
     int row, c;
-    mn_dma_target<256>((wave * CA + j) * 64 + lane, row, c);
+    mn_dma_target<BM>((wg * CA + j) * 64 + lane, row, c);
     offA[j] = group_voffset(m0 + 8 * c < d_in ? uint32_t(row * d_in + m0 + 8 * c) * 2u : kOOB, j);
+  }
+#pragma unroll
+  for (int j = 0; j < CB; ++j) {
+    int row, c;
+    mn_dma_target<BN>((wg * CB + j) * 64 + lane, row, c);
     offB[j] = group_voffset(n0 + 8 * c < d_out ? uint32_t(row * d_out + n0 + 8 * c) * 2u : kOOB, j);
   }
   const uint32_t bytesX = uint32_t(T) * uint32_t(d_in) * 2u;
   const uint32_t bytesY = uint32_t(T) * uint32_t(d_out) * 2u;
   i32x4_t rA, rB;  // buffer resources of the slice being copied (zero length past the end)
   auto prepare = [&](int st) {
-    const bool live = st < nst;
-    const int k0 = live ? st * kBK : 0;
+    const bool live = st < nst && s0 + st < all;
+    const int k0 = live ? (s0 + st) * kBK : 0;
     rA = make_rsrc_grouped(X + int64_t(k0) * d_in, live ? bytesX - uint32_t(k0) * uint32_t(d_in) * 2u : 0u);
     rB = make_rsrc_grouped(dY + int64_t(k0) * d_out, live ? bytesY - uint32_t(k0) * uint32_t(d_out) * 2u : 0u);
   };
-  const uint32_t ldsA = lds_addr(As), ldsB = lds_addr(Bs);
-  auto issue = [&](int st, int p) {
-    const int j = p % CA;
-    const uint32_t dst = (st % STAGES) * (kBK * BM * 2) + wave * CA * 1024;
+  const uint32_t ldsA = lds_addr(smem) + uint32_t(kg) * (STAGES * BM * 64);
+  const uint32_t ldsB = lds_addr(smem) + uint32_t(KS * STAGES * BM * 64) + uint32_t(kg) * (STAGES * BN * 64);
+  auto issue = [&](int st, int p) {  // copies 0 .. CA-1: X tile, CA .. CA+CB-1: dY tile
     if (p < CA)
-      dma16_group(j, rA, offA[j], ldsA + dst);
+      dma16_group(p, rA, offA[p], ldsA + (st % STAGES) * (kBK * BM * 2) + wg * CA * 1024);
     else
-      dma16_group(j, rB, offB[j], ldsB + dst);
+      dma16_group(p - CA, rB, offB[p - CA], ldsB + (st % STAGES) * (kBK * BN * 2) + wg * CB * 1024);
   };
 
   // dY^T side output (for the dX GEMM): lane (G, i) of a B fragment holds
   // dY[k0 + 8 G .. k0 + 8 G + 7, o] for o = n0 + wn*NB*16 + nb*16 + i, which is a
   // 16-byte chunk of row o of dY^T.  The tiles sharing this dY panel split
-  // the slices between them (slice kt goes to tile row kt * tiles_m / nst), and
+  // the slices between them (slice kt goes to tile row kt * tiles_m / all), and
   // within a tile the two wave rows, which hold the same B fragments, alternate.
-  auto bhook = [&](int kt, const u32x4(&bf)[NB]) {
-    if (dYt == nullptr || (kt * tiles_m) / nst != tm || (kt & 1) != wm) return;
-    const int t = kt * kBK + 8 * (lane >> 4);
-    if (t >= ldt) return;
+  // Buffer stores: one 32-bit offset per lane (out of range for rows past d_out).
+  const __amdgpu_buffer_rsrc_t rT =
+      __builtin_amdgcn_make_buffer_rsrc(dYt, short(0), int(uint32_t(d_out) * uint32_t(ldt) * 2u), 0x00020000);
+  const uint32_t offT = (uint32_t(n0 + wn * NB * 16 + (lane & 15)) * uint32_t(ldt) + 8u * uint32_t(lane >> 4)) * 2u;
+  auto bhook = [&](int st, const u32x4(&bf)[NB]) {
+    const int kt = s0 + st;
+    if (dYt == nullptr || (kt * tiles_m) / all != tm || (kt & 1) != wm) return;
+    if (kt * kBK + 8 * (lane >> 4) >= ldt) return;
 #pragma unroll
-    for (int nb = 0; nb < NB; ++nb) {
-      const int o = n0 + wn * NB * 16 + nb * 16 + (lane & 15);
-      if (o < d_out) st16(dYt + int64_t(o) * ldt + t, bf[nb]);
-    }
+    for (int nb = 0; nb < NB; ++nb)
+      __builtin_amdgcn_raw_buffer_store_b128(
+          bf[nb], rT,
+          n0 + wn * NB * 16 + nb * 16 + (lane & 15) < d_out ? offT + uint32_t(nb * 16 * ldt + kt * kBK) * 2u : kOOB, 0, 0);
   };
 
   f32x4 acc[MB][NB];
-  gemm_mainloop<MB, NB, false, false, BM, BN, PER_STAGE, STAGES, kDgateRowsAfter>(
+  constexpr int RA = CA > 2 ? kDgateRowsAfter - 1 : kDgateRowsAfter;  // four copies' offsets take a row's registers
+  gemm_mainloop<MB, NB, false, false, BM, BN, PER_STAGE, STAGES, RA>(
       As, Bs, nst, wm * 128, wn * NB * 16, lane, acc, prepare, issue, [](int) {}, bhook);
 
   // Epilogue.  Lane (l >> 4, l & 15) holds, for every (mb, nb), rows
-  // i = i0 .. i0 + 3 of column o: W[o, i0 .. i0 + 3] is one 8-byte load.
-  const int ibase = m0 + wm * 128 + 4 * (lane >> 4);
+  // i = i0 .. i0 + 3 of column o: W[o, i0 .. i0 + 3] is one 8-byte load.  The
+  // waves' sums meet in LDS once every wave has left its K-loop (its copies
+  // have drained), and are added in a fixed order.
+  int el = lane;  // opaque: the epilogue's addresses are not computed (and kept in registers) before the K-loop
+  asm volatile("" : "+v"(el));
+  const int ibase = m0 + wm * 128 + 4 * (el >> 4);
+  float* s_sum = reinterpret_cast<float*>(smem);
   if constexpr (GO > 1) {
     // Square groups (GO = G = 16 .. 128): a 16 x 16 fragment lies inside one
     // group, so each lane sums its products per group of the wave's 128 (i) x
     // 64 (o) sub-tile, and one reduction over the 64 lanes finishes the wave's
-    // share of each group.  Groups of 128 rows span two waves (wn pairs),
-    // which add their halves in a fixed order through LDS.
+    // share of each group.  Groups of 128 rows span two waves (wn pairs).
+    static_assert(NB == 4, "64 columns per wave");
     constexpr int IB = 128 / G;                  // groups along i in a wave
     constexpr int OS = GO < 64 ? 64 / GO : 1;    // groups (or group halves) along o in a wave
     float part[IB][OS];
@@ -576,7 +596,7 @@ __global__ __launch_bounds__(64 * kDgateWaves) void dgate_kernel(const uint16_t*
       for (int b = 0; b < OS; ++b) part[a][b] = 0.0f;
 #pragma unroll
     for (int nb = 0; nb < NB; ++nb) {
-      const int o = n0 + wn * NB * 16 + nb * 16 + (lane & 15);
+      const int o = n0 + wn * NB * 16 + nb * 16 + (el & 15);
 #pragma unroll
       for (int mb = 0; mb < MB; ++mb) {
         const int i0 = ibase + mb * 16;
@@ -588,6 +608,7 @@ __global__ __launch_bounds__(64 * kDgateWaves) void dgate_kernel(const uint16_t*
         }
       }
     }
+    __syncthreads();
 #pragma unroll
     for (int a = 0; a < IB; ++a)
 #pragma unroll
@@ -595,36 +616,29 @@ __global__ __launch_bounds__(64 * kDgateWaves) void dgate_kernel(const uint16_t*
         float x = part[a][b];
 #pragma unroll
         for (int d = 32; d >= 1; d >>= 1) x += __shfl_xor(x, d);
-        part[a][b] = x;
+        if (lane == 0) s_sum[(wave * IB + a) * OS + b] = x;
       }
-    const int G_out = d_out / GO;
-    if constexpr (GO < 128) {
-      if (lane == 0) {
+    __syncthreads();
+    constexpr int NV = 256 / G, NU = BN / GO;  // groups of the tile along i, along o
+    const int b = tid % NU, a = tid / NU;      // at most 256 groups (16 x 16)
+    const int u = n0 / GO + b, v = m0 / G + a;
+    if (a < NV && u < d_out / GO && v < G_in) {
+      auto sum_of = [&](int k, int n) {  // the share of K group k's wave column n
+        return s_sum[(((k * 2 + a / IB) * WN + n) * IB + a % IB) * OS + (GO < 64 ? b % OS : 0)];
+      };
+      float x = 0.0f;
 #pragma unroll
-        for (int a = 0; a < IB; ++a)
-#pragma unroll
-          for (int b = 0; b < OS; ++b) {
-            const int v = (m0 + wm * 128) / G + a;
-            const int u = (n0 + wn * 64) / GO + b;
-            if (u < G_out && v < G_in) dgate[int64_t(u) * G_in + v] = part[a][b];
-          }
+      for (int k = 0; k < KS; ++k) {
+        const float p = GO < 128 ? sum_of(k, b / OS) : sum_of(k, 2 * b) + sum_of(k, 2 * b + 1);
+        x = k == 0 ? p : x + p;
       }
-    } else {
-      float* s_half = reinterpret_cast<float*>(&As[0][0]);
-      __syncthreads();  // every wave has left its K-loop (copies drained)
-      if (lane == 0) s_half[wave] = part[0][0];
-      __syncthreads();
-      if (tid < 4) {  // group (a, b) of the tile: waves (a, 2b) and (a, 2b + 1)
-        const int a = tid >> 1, b = tid & 1;
-        const int u = n0 / GO + b, v = m0 / G + a;
-        if (u < G_out && v < G_in) dgate[int64_t(u) * G_in + v] = s_half[a * WN + 2 * b] + s_half[a * WN + 2 * b + 1];
-      }
+      dgate[int64_t(u) * G_in + v] = x;
     }
   } else {
     float part[NB][2];  // per o column: group sums over this wave's first / second 64 rows of i
 #pragma unroll
     for (int nb = 0; nb < NB; ++nb) {
-      const int o = n0 + wn * NB * 16 + nb * 16 + (lane & 15);
+      const int o = n0 + wn * NB * 16 + nb * 16 + (el & 15);
       float s0 = 0.0f, s1 = 0.0f;
 #pragma unroll
       for (int mb = 0; mb < MB; ++mb) {
@@ -644,45 +658,51 @@ __global__ __launch_bounds__(64 * kDgateWaves) void dgate_kernel(const uint16_t*
       part[nb][0] = s0;
       part[nb][1] = s1;
     }
-    if constexpr (G == 64) {
-      if (lane < 16) {
+    __syncthreads();
+    if (lane < 16) {
 #pragma unroll
-        for (int nb = 0; nb < NB; ++nb) {
-          const int o = n0 + wn * NB * 16 + nb * 16 + lane;
-          const int v = (m0 + wm * 128) / 64;
-          if (o < d_out && v < G_in) dgate[int64_t(o) * G_in + v] = part[nb][0];
-          if (o < d_out && v + 1 < G_in) dgate[int64_t(o) * G_in + v + 1] = part[nb][1];
-        }
-      }
-    } else if constexpr (G == 128) {
-      if (lane < 16) {
+      for (int nb = 0; nb < NB; ++nb)
 #pragma unroll
-        for (int nb = 0; nb < NB; ++nb) {
-          const int o = n0 + wn * NB * 16 + nb * 16 + lane;
-          const int v = (m0 + wm * 128) / 128;
-          if (o < d_out && v < G_in) dgate[int64_t(o) * G_in + v] = part[nb][0] + part[nb][1];
-        }
-      }
-    } else {
-      // The two wave rows combine through LDS, reusing the first stage buffer
-      // once every wave has finished its K-loop (their copies have drained).
-      float(*s_part)[BN] = reinterpret_cast<float(*)[BN]>(&As[0][0]);
-      __syncthreads();
-      if (lane < 16) {
+        for (int h = 0; h < 2; ++h) s_sum[((kg * 2 + wm) * 2 + h) * BN + wn * NB * 16 + nb * 16 + lane] = part[nb][h];
+    }
+    __syncthreads();
+    const int o = n0 + tid;
+    if (tid < BN && o < d_out) {
+      float q[4];  // column o's sums over each 64 rows of i
 #pragma unroll
-        for (int nb = 0; nb < NB; ++nb) s_part[wm][wn * NB * 16 + nb * 16 + lane] = part[nb][0] + part[nb][1];
+      for (int h = 0; h < 4; ++h) {
+        q[h] = s_sum[h * BN + tid];
+        if constexpr (KS == 2) q[h] += s_sum[(4 + h) * BN + tid];
       }
-      __syncthreads();
-      const int o = n0 + tid;
-      if (tid < BN && o < d_out) {
-        const float h = s_part[0][tid] + s_part[1][tid];
-        if constexpr (G == 256)
-          dgate[int64_t(o) * G_in + m0 / 256] = h;
-        else
-          atomicAdd(dgate + int64_t(o) * G_in + m0 / 512, h);
+      if constexpr (G <= 128) {
+        const int v = m0 / G;
+#pragma unroll
+        for (int a = 0; a < 256 / G; ++a)
+          if (v + a < G_in) dgate[int64_t(o) * G_in + v + a] = G == 64 ? q[a] : q[(2 * a) & 3] + q[(2 * a + 1) & 3];
+      } else if constexpr (G == 256) {
+        dgate[int64_t(o) * G_in + m0 / 256] = (q[0] + q[1]) + (q[2] + q[3]);
+      } else {
+        atomicAdd(dgate + int64_t(o) * G_in + m0 / 512, (q[0] + q[1]) + (q[2] + q[3]));
       }
     }
   }
+}
+
+template <int G, int GO>
+__global__ __launch_bounds__(64 * kDgateWaves) void dgate_kernel(const uint16_t* __restrict__ dY, const uint16_t* __restrict__ X,
+                                                    const uint16_t* __restrict__ W, int T, int d_in, int d_out,
+                                                    float* __restrict__ dgate, uint16_t* __restrict__ dYt, int ldt,
+                                                    ListArgs la) {
+  dgate_tile<G, GO, 256, 1>(dY, X, W, T, d_in, d_out, dgate, dYt, ldt, la);
+}
+
+// 256 x BN tiles, K over two wave groups.
+template <int G, int GO, int BN>
+__global__ __launch_bounds__(64 * kDgateWaves) void dgate_k2_kernel(const uint16_t* __restrict__ dY, const uint16_t* __restrict__ X,
+                                                       const uint16_t* __restrict__ W, int T, int d_in, int d_out,
+                                                       float* __restrict__ dgate, uint16_t* __restrict__ dYt, int ldt,
+                                                       ListArgs la) {
+  dgate_tile<G, GO, BN, 2>(dY, X, W, T, d_in, d_out, dgate, dYt, ldt, la);
 }
 
 // Fill n floats with zero (before the order-independent two-tile accumulation).
@@ -933,6 +953,8 @@ __global__ __launch_bounds__(256) void transpose_kernel(const uint16_t* __restri
 // The group shapes built: 1 x {64, 128, 256, 512} and square {16, 32, 64, 128}.
 #define GM_CASE_G(KERNEL, G, GO, GRID, THREADS, ...) \
   case (G << 8) | GO: hipLaunchKernelGGL((KERNEL<G, GO>), dim3(GRID), dim3(THREADS), 0, s, __VA_ARGS__); break;
+#define GM_CASE_G1(KERNEL, G, GRID, THREADS, ...) \
+  case G: hipLaunchKernelGGL((KERNEL<G, 1>), dim3(GRID), dim3(THREADS), 0, s, __VA_ARGS__); break;
 #define GM_CASES_G64(KERNEL, GRID, THREADS, ...)                 \
     GM_CASE_G(KERNEL, 64, 1, GRID, THREADS, __VA_ARGS__)         \
     GM_CASE_G(KERNEL, 128, 1, GRID, THREADS, __VA_ARGS__)        \
@@ -1018,10 +1040,14 @@ hipError_t launch_fwd_packed(const uint16_t* X, const uint16_t* Wp, const int* c
   return hipGetLastError();
 }
 
+template <int G, int GO>
+constexpr auto dgate_half = dgate_k2_kernel<G, GO, 128>;
+template <int G, int GO>
+constexpr auto dgate_low = dgate_k2_kernel<G, GO, 64>;
+
 hipError_t launch_dgate(const uint16_t* dY, const uint16_t* X, const uint16_t* W, int T, int d_in, int d_out, int g,
                         int go, float* dgate, uint16_t* dYt, int ldt, const float* mask, int nsub, int* colcount,
                         int* colsoft, int* rows, float* scales, int* subbits, hipStream_t s) {
-  const int tiles = ((d_out + 255) / 256) * ((d_in + 255) / 256);
   ListArgs la{mask, 0, (d_out + kListChunk - 1) / kListChunk, nsub, colcount, colsoft, rows, subbits, scales};
   if (colcount) la.nunits = (d_in / g / nsub) * la.nchunks;
   if (g == 512) {
@@ -1031,7 +1057,30 @@ hipError_t launch_dgate(const uint16_t* dY, const uint16_t* X, const uint16_t* W
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
   }
-  GM_LAUNCH_G(dgate_kernel, tiles + la.nunits, 64 * kDgateWaves, dY, X, W, T, d_in, d_out, dgate, dYt, ldt, la)
+  auto tiles = [&](int bn) { return ((d_in + 255) / 256) * ((d_out + bn - 1) / bn); };
+  // The tile with the lowest estimated time: rounds of 256 blocks (a partly
+  // empty last round costs a whole one) of 13 us + 0.62 us per K slice for 256 x
+  // 256, 13 + 0.415 for 256 x 128, 7 + 0.32 for 256 x 64 (1 x g groups only: its
+  // waves hold 32 columns).  E.g. 1024 x 1024, T = 2048: 49 us in 256 x 256, 40 in
+  // 256 x 128, 26 in 256 x 64; 2816 x 2056, T = 1000: 34 / 27 / 33; 4096 x 4096, T
+  // = 2048: 61 / 80 / 104.
+  const int64_t sl = (T + 31) / 32;
+  auto est = [&](int bn, int64_t ns) { return int64_t((tiles(bn) + 255) / 256) * ns; };
+  const int64_t big = est(256, 13000 + 620 * sl), half = est(128, 13000 + 415 * sl),
+                low = go == 1 ? est(64, 7000 + 320 * sl) : INT64_MAX;
+  if (low < half && low < big) {
+    switch (g) {
+      GM_CASE_G1(dgate_low, 64, tiles(64) + la.nunits, 64 * kDgateWaves, dY, X, W, T, d_in, d_out, dgate, dYt, ldt, la)
+      GM_CASE_G1(dgate_low, 128, tiles(64) + la.nunits, 64 * kDgateWaves, dY, X, W, T, d_in, d_out, dgate, dYt, ldt, la)
+      GM_CASE_G1(dgate_low, 256, tiles(64) + la.nunits, 64 * kDgateWaves, dY, X, W, T, d_in, d_out, dgate, dYt, ldt, la)
+      GM_CASE_G1(dgate_low, 512, tiles(64) + la.nunits, 64 * kDgateWaves, dY, X, W, T, d_in, d_out, dgate, dYt, ldt, la)
+      default: return hipErrorInvalidValue;
+    }
+  } else if (half < big) {
+    GM_LAUNCH_G(dgate_half, tiles(128) + la.nunits, 64 * kDgateWaves, dY, X, W, T, d_in, d_out, dgate, dYt, ldt, la)
+  } else {
+    GM_LAUNCH_G(dgate_kernel, tiles(256) + la.nunits, 64 * kDgateWaves, dY, X, W, T, d_in, d_out, dgate, dYt, ldt, la)
+  }
   return hipGetLastError();
 }
 

@@ -1,12 +1,12 @@
 """GPU parity of the backward GEMMs' tiles against the fp64 oracle, at tile edges: dX over column lists in its
-64- to 256-column tiles with and without two K groups, dX of 16 x 16 and 32 x 32 groups over every row, and the LM
-head's backward in each of its tiles."""
+64- to 256-column tiles with and without two K groups, dX of 16 x 16 and 32 x 32 groups over every row, dgate in its
+256-, 128- and 64-column tiles, and the LM head's backward in each of its tiles."""
 import numpy as np
 import pytest
 
 import oracle
 import workloads
-from gpu_support import (assert_close, dev_bf16, dev_f32, empty_bf16, empty_f32, host_bits, host_f64_from_bf16, ref_dx,
+from gpu_support import (assert_close, dev_bf16, dev_f32, empty_bf16, empty_f32, host_bits, host_f64_from_bf16, ref_dgate, ref_dx,
                          say, sync, workspace)
 
 pytestmark = pytest.mark.gpu
@@ -58,6 +58,39 @@ def test_dx_tiles(T, d_in, d_out, g, g_out, soft):
     dX = _dx(case, mask, True)
     assert_close("dX", host_f64_from_bf16(dX), ref, bound=b)
     assert np.array_equal(host_bits(dX), host_bits(_dx(case, mask, False))), "dX differs without dgate beside it"
+
+
+@pytest.mark.parametrize("T,d_in,d_out,g,g_out", [
+    (1, 64, 8, 64, 1),          # 256 x 64 tiles, one slice: the second K group has none
+    (33, 192, 72, 64, 1),       # a row past the first tile, columns past 128
+    (100, 1024, 1000, 512, 1),  # two tiles add to a group
+    (70, 640, 264, 128, 1),
+    (1000, 2816, 2056, 128, 1),  # 256 x 128 tiles
+    (900, 4096, 1032, 256, 1),
+    (650, 4096, 1000, 64, 1),
+    (700, 4096, 2000, 512, 1),
+    (40, 320, 336, 16, 16),     # square groups in 256 x 128 tiles
+    (33, 320, 160, 32, 32),
+    (200, 832, 448, 64, 64),
+    (65, 384, 384, 128, 128),
+    (300, 4096, 4096, 128, 128),  # 256 x 256 tiles
+    (130, 4096, 3848, 64, 1),
+])
+def test_dgate_tiles(T, d_in, d_out, g, g_out):
+    say(f"dgate tiles: T={T} d_in={d_in} d_out={d_out} g={g} g_out={g_out}")
+    import paper_2609_33977_amd as gm
+    case = workloads.make_linear_case((293, T, d_in, d_out, g), T, d_in, d_out, g, None, g_out=g_out)
+    dgate, dX = empty_f32(*case.mask.shape), empty_bf16(T, d_in)
+    ws = workspace(gm.gm_workspace_size(gm.GM_OP_BWD, T, d_in, d_out, g, g_out))
+    dY, X, W = dev_bf16(case.dY), dev_bf16(case.X), dev_bf16(case.W)
+    gm.gm_masked_linear_bwd(dY, X, W, dev_f32(case.mask), g, dX, dgate, ws, g_out=g_out)
+    sync()
+    ref, b = ref_dgate(oracle.from_bf16(case.dY), oracle.from_bf16(case.X), oracle.from_bf16(case.W), g, g_out)
+    assert_close("dgate", dgate.cpu().numpy(), ref, bound=b)
+    alone = empty_f32(*case.mask.shape)
+    gm.gm_masked_linear_bwd(dY, X, W, None, g, None, alone, None, g_out=g_out)
+    sync()
+    assert np.array_equal(alone.cpu().numpy(), dgate.cpu().numpy()), "dgate differs without dX beside it"
 
 
 @pytest.mark.parametrize("N,d,V", [
