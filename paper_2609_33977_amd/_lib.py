@@ -10,6 +10,8 @@ from __future__ import annotations
 import ctypes
 import os
 
+import torch
+
 HERE = os.path.dirname(os.path.abspath(__file__))
 # GM_LIBRARY_PATH selects another build of the same library (the host-sanitizer
 # build of the CPU tests); by default the in-tree build is loaded.
@@ -39,8 +41,7 @@ def _load() -> ctypes.CDLL:
     # torch carries its own copy of the HIP runtime and names it without the
     # version suffix, so the dynamic linker would load the system copy for
     # this library if it came first; a second runtime in the process sees no
-    # device.  Loading torch first makes this library bind to torch's runtime.
-    import torch  # noqa: F401
+    # device.  torch, imported above, makes this library bind to its runtime.
     lib = ctypes.CDLL(LIB_PATH)
     P, I64, I32, F32, SZ = ctypes.c_void_p, ctypes.c_int64, ctypes.c_int32, ctypes.c_float, ctypes.c_size_t
     F64 = ctypes.c_double
@@ -96,7 +97,7 @@ def _ptr(t):
         raise ValueError("tensor must be contiguous")
     if not t.is_cuda:
         raise ValueError("tensor must live on the GPU")
-    return ctypes.c_void_p(t.data_ptr())
+    return t.data_ptr()
 
 
 # Argument checks run before any call into the library: the C entry points see
@@ -105,10 +106,13 @@ def _ptr(t):
 # dtype and size are checked first; _ptr then checks layout and device as it
 # takes each pointer.
 
-def _dt(name):
-    import torch
-    return {"bf16": torch.bfloat16, "f32": torch.float32, "f64": torch.float64, "i32": torch.int32,
-            "i64": torch.int64, "u8": torch.uint8}[name]
+# These run for every argument of every call (15 of them in the three selector
+# calls of one decoder layer, whose kernels take under 20 us), so they look
+# nothing up twice and make no objects.
+
+_DTYPES = {"bf16": torch.bfloat16, "f32": torch.float32, "f64": torch.float64, "i32": torch.int32,
+           "i64": torch.int64, "u8": torch.uint8}
+_U64 = torch.uint64
 
 
 def _arg(where, what, t, dtype, shape=None, numel=None, at_least=None, optional=False):
@@ -117,14 +121,13 @@ def _arg(where, what, t, dtype, shape=None, numel=None, at_least=None, optional=
         if optional:
             return
         raise ValueError(f"{where}: {what} is required")
-    want = _dt(dtype)
-    if dtype == "i64" and str(t.dtype) == "torch.uint64":
-        want = t.dtype  # counters may be handed over as unsigned 64-bit
-    if t.dtype != want:
+    want = _DTYPES[dtype]
+    if t.dtype is not want and not (dtype == "i64" and t.dtype is _U64):  # counters may be handed over as unsigned
         raise ValueError(f"{where}: {what} must be {want}, got {t.dtype}")
     if shape is not None:
-        if t.dim() != len(shape) or any(w is not None and int(d) != int(w) for d, w in zip(t.shape, shape)):
-            raise ValueError(f"{where}: {what} must have shape {tuple(shape)}, got {tuple(t.shape)}")
+        have = t.shape
+        if len(have) != len(shape) or any(w is not None and d != int(w) for d, w in zip(have, shape)):
+            raise ValueError(f"{where}: {what} must have shape {tuple(shape)}, got {tuple(have)}")
     if numel is not None and t.numel() != numel:
         raise ValueError(f"{where}: {what} must hold {numel} elements, got {t.numel()}")
     if at_least is not None and t.numel() < at_least:
@@ -138,9 +141,11 @@ def _groups(d_out, d_in, g, g_out, where):
 
 
 def _stream(stream):
-    import torch
-    s = torch.cuda.current_stream() if stream is None else stream
-    return ctypes.c_void_p(s.cuda_stream)
+    # The current stream's handle without a Stream object around it (torch is
+    # initialised: the tensors' pointers were taken before).
+    if stream is None:
+        return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+    return stream.cuda_stream
 
 
 def gm_gate(logits, noise, tau: float, hard: bool, mask_out, soft_out=None, stream=None) -> None:
