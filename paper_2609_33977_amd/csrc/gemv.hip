@@ -154,7 +154,9 @@ typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 
 // XL: X goes through LDS (see the K loop); the launcher picks it for blocks of
 // 64 rows, or more than 8 tokens, where it measured 2-5 % faster.
-template <int RT, bool PACKED, bool XL>
+// MF: floats of the staged tables.  With tables for kMmaMaskFloats the LDS of a
+// 32-row block (80 KiB and more) kept a second one off the CU.
+template <int RT, bool PACKED, bool XL, int MF>
 __global__ __launch_bounds__(64 * kMmaWaves) void gemv_mfma_kernel(const uint16_t* __restrict__ X,
                                                                   const uint16_t* __restrict__ W,
                                                                   const float* __restrict__ mask,
@@ -165,11 +167,12 @@ __global__ __launch_bounds__(64 * kMmaWaves) void gemv_mfma_kernel(const uint16_
                                                                   uint16_t* __restrict__ Y) {
   constexpr int R = 16 * RT;
   constexpr int NT = 64 * kMmaWaves;
-  __shared__ float s_m[kMmaMaskFloats];
-  __shared__ int s_idx[PACKED ? kMmaMaskFloats : 1];  // packed: piece of (row, group) from the block's first piece
+  __shared__ float s_m[MF];
+  __shared__ int s_idx[PACKED ? MF : 1];  // packed: piece of (row, group) from the block's first piece
   __shared__ int s_rp[PACKED ? R + 1 : 1];
-  __shared__ f32x4 s_part[kMmaWaves][RT][64];
-  __shared__ u32x4 s_x[kMmaWaves][XL ? 4 * 64 : 1];  // XL: per wave, the X slices of one load batch
+  // Per wave: its partial tiles, after the K loop (XL: in the K loop, the X slices of one load batch).
+  __shared__ u32x4 s_x[kMmaWaves][XL ? 4 * 64 : RT * 64];
+  f32x4(*s_part)[XL ? 4 : RT][64] = reinterpret_cast<f32x4(*)[XL ? 4 : RT][64]>(s_x);
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int o0 = blockIdx.x * R;
   const int G_in = d_in / g;
@@ -526,32 +529,53 @@ static hipError_t gemv_passes(const uint16_t* X, const uint16_t* W, const float*
 }
 
 // The 2..16 token MFMA kernel when its staged tables fit in LDS and its byte
-// offsets fit in 32 bits: four row tiles while that still gives 192 blocks or
-// more, else two, fewer when the block's tables do not fit.  Returns false
-// (nothing launched) otherwise.
+// offsets fit in 32 bits.  Returns false (nothing launched) otherwise.
+//
+// Rows per block.  64-row blocks take 160 registers, so one is resident per CU;
+// 32- and 16-row blocks (with the smaller tables) run two to four per CU, which
+// overlap each other's load batches.  16 rows while that is at most one block
+// per CU (2048 x 5632, T = 8: 8.9 us against 11.3 in 32-row blocks, 10.4 / 13.6
+// packed).  64 rows where such blocks fill one round of the CUs (192 .. 256
+// blocks) and two of these hold: more than 8 tokens (X is read half as often),
+// in place, few selectors staged (15360 x 5120, 32-row / 64-row blocks: T = 16
+// 23.8 / 21.6 in place, 25.8 / 24.0 packed; T = 8 20.7 / 20.3 and 23.1 / 23.7; 64
+// groups wide T = 8 22.4 / 23.7); beyond one round where all three hold and the
+// last round is well filled (27648 x 5120, T = 16 in place 40.6 / 39.9).  32
+// rows otherwise (27648 x 5120, T = 8: 35.2 / 37.8, packed 40.5 / 45.1).
 template <bool PACKED>
 static bool launch_mfma(const uint16_t* X, const uint16_t* W, const float* mask, const int* chunk, const float* scale,
                         const int* rowptr, int T, int d_in, int d_out, int g, int go, uint16_t* Y, hipStream_t s,
                         hipError_t& err) {
   const int G_in = d_in / g;
-  auto fits = [&](int R) { return (go == 1 ? R : (R > go ? R / go : 1)) * G_in <= kMmaMaskFloats; };
-  int rt = (d_out + 63) / 64 >= 192 ? 4 : 2;
+  auto table = [&](int R) { return (go == 1 ? R : (R > go ? R / go : 1)) * G_in; };
+  auto fits = [&](int R) { return table(R) <= kMmaMaskFloats; };
+  const int b64 = (d_out + 63) / 64;
+  const int votes = int(T > 8) + int(!PACKED) + int(table(64) <= 2048);
+  const bool rows64 = b64 > 256 ? votes == 3 && (b64 - 1) % 256 >= 160 : b64 >= 192 && votes >= 2;
+  int rt = (d_out + 15) / 16 <= 256 ? 1 : rows64 ? 4 : 2;
   while (rt > 1 && !fits(16 * rt)) rt /= 2;
   // byte offsets into the block's rows of W (or its pieces) and into X are 32-bit, below the out-of-range marker
   const int64_t span = int64_t(16 * rt > T ? 16 * rt : T) * d_in * 2;
   if (!fits(16 * rt) || span >= int64_t(kOutOfRange)) return false;
   const dim3 grid(unsigned((d_out + 16 * rt - 1) / (16 * rt))), block(64 * kMmaWaves);
   const bool xl = rt == 4 || T > 8;
-#define GM_MFMA_LAUNCH(RTV, XLV)                                                                                  \
-  hipLaunchKernelGGL((gemv_mfma_kernel<RTV, PACKED, XLV>), grid, block, 0, s, X, W, mask, chunk, scale, rowptr, T, \
-                     d_in, d_out, g, go, Y)
-  if (rt == 4) {
-    if (xl) GM_MFMA_LAUNCH(4, true); else GM_MFMA_LAUNCH(4, false);
-  } else if (rt == 2) {
-    if (xl) GM_MFMA_LAUNCH(2, true); else GM_MFMA_LAUNCH(2, false);
-  } else {
-    if (xl) GM_MFMA_LAUNCH(1, true); else GM_MFMA_LAUNCH(1, false);
+#define GM_MFMA_LAUNCH(RTV, XLV, MFV)                                                                             \
+  hipLaunchKernelGGL((gemv_mfma_kernel<RTV, PACKED, XLV, MFV>), grid, block, 0, s, X, W, mask, chunk, scale, rowptr, \
+                     T, d_in, d_out, g, go, Y)
+#define GM_MFMA_TABLES(RTV, MFV)                                                          \
+  if (table(16 * RTV) <= MFV) {                                                           \
+    if (xl) GM_MFMA_LAUNCH(RTV, true, MFV); else GM_MFMA_LAUNCH(RTV, false, MFV);         \
+  } else {                                                                                \
+    if (xl) GM_MFMA_LAUNCH(RTV, true, kMmaMaskFloats); else GM_MFMA_LAUNCH(RTV, false, kMmaMaskFloats); \
   }
+  if (rt == 4) {
+    GM_MFMA_LAUNCH(4, true, kMmaMaskFloats);
+  } else if (rt == 2) {
+    GM_MFMA_TABLES(2, 4096)
+  } else {
+    GM_MFMA_TABLES(1, 2048)
+  }
+#undef GM_MFMA_TABLES
 #undef GM_MFMA_LAUNCH
   err = hipGetLastError();
   return true;
