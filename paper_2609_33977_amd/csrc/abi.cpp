@@ -131,7 +131,11 @@ size_t fwd_workspace(int64_t T, int64_t d_in, int64_t d_out, int32_t g) {
 // fill, epilogue) and a time per 32-deep K slice.  Measured (4096 x 4096, half the groups kept): 256 x 256 tiles 15 us + 0.66
 // us per slice; 256 x 128 (K over two wave groups) 14 us + 0.42; 128 x 128
 // (same) 9 us + 0.25; a K split over blocks adds a reduction of 4 us and 8
-// bytes per output and share (mostly cached: 15 TB/s).  The model picks the
+// bytes per output and share (mostly cached: 15 TB/s for the few shares of 256 x
+// 256 tiles, 8 TB/s for up to eight of 128 x 128 ones).  Splitting the smaller
+// tile: 4096 x 4096, T = 128 22 us (unsplit 38, 256 x 256 split in eight 28), T =
+// 512 31 (39, 40); 4096 x 11008 inputs, T = 128 28 (92, 44); 2816 x 2056, T = 300
+// 19 (28, 29).  The model picks the
 // fastest or within 3 % of it at T = 128 .. 4096 on 1024^2, 2816 x 2056, 4096^2,
 // 11008 x 4096 (both ways) and the LLaMA-2-13B shapes: e.g. T = 2048 at 4096^2
 // 65 us in 256 x 128 tiles (256 x 256 split in two: 73), T = 1024 41 us in 128 x
@@ -153,15 +157,20 @@ FwdPlan fwd_plan(int64_t T, int64_t d_in, int64_t d_out, int32_t g, int32_t g_ou
   using gm::FwdTile;
   const int64_t slices = d_in / 32;
   auto tiles = [&](int64_t bm, int64_t bn) { return ((d_out + bm - 1) / bm) * ((T + bn - 1) / bn); };
+  auto reduce_ns = [&](int64_t k, int64_t rate) { return 4000 + k * T * d_out * 8 / rate; };  // rate: bytes per ns
   FwdPlan best{FwdTile::k128x128, 1};
   int64_t best_ns = gm::rounds_ns(tiles(128, 128), 9000 + 250 * slices);
+  for (int k = 2; k <= ks; ++k) {  // ks: what the workspace holds
+    const int64_t ns = gm::rounds_ns(tiles(128, 128) * k, 9000 + 250 * slices / k) + reduce_ns(k, 8000);
+    if (ns < best_ns) best = {FwdTile::k128x128, k}, best_ns = ns;
+  }
   if (fwd_tile_fits(FwdTile::k256x128, d_in, g, g_out, packed)) {
     const int64_t ns = gm::rounds_ns(tiles(256, 128), 14000 + 420 * slices);
     if (ns < best_ns) best = {FwdTile::k256x128, 1}, best_ns = ns;
   }
   if (fwd_tile_fits(FwdTile::k256x256, d_in, g, g_out, packed)) {
     int64_t ns = gm::rounds_ns(tiles(256, 256) * ks, 15000 + 660 * slices / ks);
-    if (ks > 1) ns += 4000 + ks * T * d_out * 8 / 15000;
+    if (ks > 1) ns += reduce_ns(ks, 15000);
     if (ns < best_ns) best = {FwdTile::k256x256, ks}, best_ns = ns;
   }
   return best;

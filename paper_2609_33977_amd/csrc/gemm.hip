@@ -62,7 +62,7 @@ constexpr int kFwdRowsAfter = 4, kDgateRowsAfter = 4, kDxRowsAfter = 1;
 // units that some row of the tile keeps; inside a visited unit each 16-byte
 // chunk of W whose group is pruned for its row is zero-filled instead of read.
 //
-// Split K (ksplit > 1, for launches with fewer tiles than half the CUs):
+// Split K (ksplit > 1, 256 x 256 and 128 x 128 tiles, for launches with fewer tiles than half the CUs):
 // block b works on tile b / ksplit and takes share b % ksplit of the tile's
 // list of visited units (contiguous, in order), and stores its fp32 partial
 // tile into part[share][t][o]; fwd_reduce_kernel then adds the shares in
@@ -435,6 +435,16 @@ __global__ __launch_bounds__(64 * kFwdWaves) void fwd_kernel(const uint16_t* __r
     store_tile_rows<BM, MB, NB, NW>(acc, reinterpret_cast<char*>(&As[0][0]), reinterpret_cast<char*>(&Bs[0][0]), wm,
                                     wn, tid, lane, Y, d_out, n0, T, m0, d_out);
   } else {
+    if constexpr (BM == 128 && !PACKED) {
+      if (part) {
+        ksum2<BM, BN, MB, NB, NW, HC>(acc, reinterpret_cast<f32x4*>(smem), kg, wg, wm, wn, lane,
+                                      [&](int m, int n, const f32x4& sum) {
+                                        if (n0 + n < T && m0 + m < d_out)
+                                          *reinterpret_cast<f32x4*>(part + (int64_t(share) * T + n0 + n) * d_out + m0 + m) = sum;
+                                      });
+        return;
+      }
+    }
     store_tile_ksum2<BM, BN, MB, NB, NW, HC>(acc, reinterpret_cast<f32x4*>(smem),
                                              reinterpret_cast<char*>(smem) + NW * HC * NB * 1024, kg, wg, wm, wn, tid,
                                              lane, Y, d_out, n0, T, m0, d_out);
@@ -984,12 +994,12 @@ static int fwd_tiles(FwdTile tile, int T, int d_out) {
 
 hipError_t launch_fwd(const uint16_t* X, const uint16_t* W, const float* mask, int T, int d_in, int d_out, int g,
                       int go, uint16_t* Y, FwdTile tile, int ksplit, float* part, hipStream_t s) {
-  if (ksplit < 1 || (ksplit > 1 && (part == nullptr || tile != FwdTile::k256x256))) return hipErrorInvalidValue;
+  if (ksplit < 1 || (ksplit > 1 && (part == nullptr || tile == FwdTile::k256x128))) return hipErrorInvalidValue;
   const PackedArgs none{nullptr, nullptr, nullptr};
   float* p = ksplit > 1 ? part : nullptr;
   const int blocks = fwd_tiles(tile, T, d_out) * ksplit;
   if (tile == FwdTile::k128x128) {
-    GM_LAUNCH_G(fwd_mid, blocks, 64 * kFwdWaves, X, W, mask, T, d_in, d_out, Y, 1, p, none)
+    GM_LAUNCH_G(fwd_mid, blocks, 64 * kFwdWaves, X, W, mask, T, d_in, d_out, Y, ksplit, p, none)
   } else if (tile == FwdTile::k256x128) {
     if (g == 16) return hipErrorInvalidValue;
     switch ((g << 8) | go) {

@@ -246,18 +246,17 @@ __device__ __forceinline__ void store_tile_rows(const f32x4 (&acc)[MB][NB], char
   }
 }
 
-// The same output for a tile whose K range was split over two wave groups
-// kg = 0, 1 (each 2 (m) x NW/4 (n) waves holding the whole BM x BN tile): each
-// wave hands the other group's wave with the same fragments half of them
-// through LDS (fragment rows [0, MB/2) to group 0, the rest to group 1, HC rows
-// at a time), adds the half it got to its own (two addends: the same sum
-// whichever is first), and the bf16 rows go out as above.  xch: NW HC NB KiB;
-// rows: 2 BM BN bytes (another buffer).
-template <int BM, int BN, int MB, int NB, int NW, int HC>
-__device__ __forceinline__ void store_tile_ksum2(const f32x4 (&acc)[MB][NB], f32x4* xch, char* rows, int kg, int wg,
-                                                 int wm, int wn, int tid, int lane, uint16_t* __restrict__ out,
-                                                 int64_t ld, int r0, int rlim, int c0, int clim) {
-  constexpr int NG = NW / 2, H = MB / 2, CPR = BM / 8;
+// Sum of a tile whose K range was split over two wave groups kg = 0, 1 (each
+// 2 (m) x NW/4 (n) waves holding the whole BM x BN tile): each wave hands the
+// other group's wave with the same fragments half of them through LDS
+// (fragment rows [0, MB/2) to group 0, the rest to group 1, HC rows at a
+// time), adds the half it got to its own (two addends: the same sum whichever
+// is first) and passes every four sums to emit(m, n, sum), rows m .. m + 3 of
+// column n.  xch: NW HC NB KiB.  Ends with a barrier.
+template <int BM, int BN, int MB, int NB, int NW, int HC, class Emit>
+__device__ __forceinline__ void ksum2(const f32x4 (&acc)[MB][NB], f32x4* xch, int kg, int wg, int wm, int wn, int lane,
+                                      Emit&& emit) {
+  constexpr int NG = NW / 2, H = MB / 2;
   static_assert(MB * 32 == BM && NB * 16 * (NG / 2) == BN && MB % 2 == 0 && H % HC == 0, "tile shape");
   auto finish = [&](auto own) {
     constexpr int O = decltype(own)::value;  // fragment rows this group keeps: [O, O + H)
@@ -273,15 +272,9 @@ __device__ __forceinline__ void store_tile_ksum2(const f32x4 (&acc)[MB][NB], f32
 #pragma unroll
       for (int q = 0; q < HC; ++q)
 #pragma unroll
-        for (int nb = 0; nb < NB; ++nb) {
-          const f32x4 sum = acc[O + h + q][nb] + xch[((((1 - kg) * NG + wg) * HC + q) * NB + nb) * 64 + lane];
-          const int m = wm * (BM / 2) + (O + h + q) * 16 + 4 * (lane >> 4);
-          const int n = wn * NB * 16 + nb * 16 + (lane & 15);
-          uint2 w;
-          w.x = pack_bf16x2(sum[0], sum[1]);
-          w.y = pack_bf16x2(sum[2], sum[3]);
-          *reinterpret_cast<uint2*>(rows + n * (2 * BM) + (((m >> 3) ^ (n & (CPR - 1))) << 4) + ((m >> 2) & 1) * 8) = w;
-        }
+        for (int nb = 0; nb < NB; ++nb)
+          emit(wm * (BM / 2) + (O + h + q) * 16 + 4 * (lane >> 4), wn * NB * 16 + nb * 16 + (lane & 15),
+               acc[O + h + q][nb] + xch[((((1 - kg) * NG + wg) * HC + q) * NB + nb) * 64 + lane]);
     }
     __syncthreads();
   };
@@ -289,6 +282,21 @@ __device__ __forceinline__ void store_tile_ksum2(const f32x4 (&acc)[MB][NB], f32
     finish(std::integral_constant<int, 0>{});
   else
     finish(std::integral_constant<int, H>{});
+}
+
+// The output of such a tile: the sums go out as whole bf16 rows, as above.
+// rows: 2 BM BN bytes (another buffer than xch).
+template <int BM, int BN, int MB, int NB, int NW, int HC>
+__device__ __forceinline__ void store_tile_ksum2(const f32x4 (&acc)[MB][NB], f32x4* xch, char* rows, int kg, int wg,
+                                                 int wm, int wn, int tid, int lane, uint16_t* __restrict__ out,
+                                                 int64_t ld, int r0, int rlim, int c0, int clim) {
+  constexpr int CPR = BM / 8;
+  ksum2<BM, BN, MB, NB, NW, HC>(acc, xch, kg, wg, wm, wn, lane, [&](int m, int n, const f32x4& sum) {
+    uint2 w;
+    w.x = pack_bf16x2(sum[0], sum[1]);
+    w.y = pack_bf16x2(sum[2], sum[3]);
+    *reinterpret_cast<uint2*>(rows + n * (2 * BM) + (((m >> 3) ^ (n & (CPR - 1))) << 4) + ((m >> 2) & 1) * 8) = w;
+  });
 #pragma unroll 4
   for (int k = 0; k < BN * CPR / (64 * NW); ++k) {
     const int e = k * 64 * NW + tid, n = e / CPR, c = e % CPR;

@@ -51,7 +51,7 @@ constexpr int fwd_max_groups(int g, bool packed, bool half) {
   return packed && half && 16384 / g > 128 ? 128 : 16384 / g;
 }
 
-// ksplit > 1 (256 x 256 tiles) splits each tile's K range over that many blocks, which store fp32
+// ksplit > 1 (256 x 256 and 128 x 128 tiles) splits each tile's K range over that many blocks, which store fp32
 // partial tiles into part [ksplit][T][d_out]; a second kernel adds them in order.
 hipError_t launch_fwd(const uint16_t* X, const uint16_t* W, const float* mask, int T, int d_in, int d_out, int g,
                       int go, uint16_t* Y, FwdTile tile, int ksplit, float* part, hipStream_t s);
