@@ -7,9 +7,9 @@
 // Groups are g_out x g blocks (Sec. 2.1): u(o) = o / g_out is the mask row of
 // output row o, v(i) = i / g its mask column; 1 x g groups have g_out = 1.
 //
-// Shared machinery (gm_gemm.h, gm_pipe.h): 256 x 256 output tiles (smaller forward
-// tiles for launches that would leave the chip part empty; dX:
-// min(max(g, 64), 256) x 256), eight waves of 128 x 64 (dX tiles of 64 rows:
+// Shared machinery (gm_gemm.h, gm_pipe.h): 256 x 256 output tiles (smaller ones,
+// most with K over two wave groups, for launches that would leave the chip part
+// empty; dX: at most max(g, 64) rows), eight waves of 128 x 64 (dX tiles of 64 rows:
 // four waves of 32 x 128) accumulated in AGPRs and VGPRs with
 // v_mfma_f32_16x16x32_bf16, and a four-stage pipeline of 32-deep K slices
 // copied global -> LDS by buffer loads with the lds modifier (no registers in
