@@ -821,6 +821,9 @@ __global__ __launch_bounds__(64 * dx_waves(BM, KS)) void dx_kernel(const uint16_
     colB[j] = group_voffset(uint32_t(16 * c), j);
     pastB[j] = uint32_t(n0 + 8 * c >= ldt) << 31;
   }
+  // Entries past the column's count were never written: their offsets are
+  // replaced, not only flagged (a flagged offset near 2^32 would wrap into
+  // range when the copy's bias is added).
   uint32_t offA[NA], offB[NBC];  // this slice's per-lane offsets
   auto prepare = [&](int st) {
     if constexpr (KS == 1) {
@@ -831,14 +834,15 @@ __global__ __launch_bounds__(64 * dx_waves(BM, KS)) void dx_kernel(const uint16_
         mn_dma_target<BM>((wg * NA + j) * 64 + lane, row, c);
         bool dead = k0 + row >= kv;
         if constexpr (NSUB > 1) dead |= ((pick(kbits, j, RPI_A, lane / (BM / 8)) >> (c / CPS)) & 1) == 0;
-        offA[j] = group_voffset(uint32_t(pick(idx, j, RPI_A, lane / (BM / 8)) * d_in + 8 * c) * 2u | uint32_t(dead) << 31, j);
+        const uint32_t at = uint32_t(pick(idx, j, RPI_A, lane / (BM / 8)) * d_in + 8 * c) * 2u;
+        offA[j] = group_voffset(dead ? kOOB : at, j);
       }
 #pragma unroll
       for (int j = 0; j < NBC; ++j) {
         int row, c;
         mn_dma_target<BN>((wg * NBC + j) * 64 + lane, row, c);
-        offB[j] = group_voffset(uint32_t(pick(idx, j, RPI_B, lane / (BN / 8)) * ldt + 8 * c) * 2u |
-                                uint32_t(k0 + row >= kv || n0 + 8 * c >= ldt) << 31, j);
+        const uint32_t at = uint32_t(pick(idx, j, RPI_B, lane / (BN / 8)) * ldt + 8 * c) * 2u;
+        offB[j] = group_voffset(k0 + row >= kv || n0 + 8 * c >= ldt ? kOOB : at, j);
       }
       load_idx(st + 1);
       return;

@@ -60,6 +60,31 @@ def test_dx_tiles(T, d_in, d_out, g, g_out, soft):
     assert np.array_equal(host_bits(dX), host_bits(_dx(case, mask, False))), "dX differs without dgate beside it"
 
 
+@pytest.mark.parametrize("fill", [0xFF, 0x7F])
+@pytest.mark.parametrize("T,d_in,d_out,g,g_out", [
+    (17, 64, 40, 64, 1),     # offsets of the unwritten entry -1 end just below 2^32
+    (96, 128, 104, 64, 1),
+    (1000, 192, 72, 64, 1),
+    (1000, 16384, 128, 64, 64),
+    (2050, 4096, 264, 128, 1),
+    (4090, 4096, 520, 256, 1),
+])
+def test_dx_does_not_read_unwritten_list_entries(T, d_in, d_out, g, g_out, fill):
+    """A column's list ends after its kept rows; the entries up to the end of the last 32-row slice hold whatever
+    the workspace held, here 0xFF bytes (row -1, selector NaN), and must not choose an address."""
+    import paper_2609_33977_amd as gm
+    say(f"dX, workspace of {fill:#x} bytes: T={T} d_in={d_in} d_out={d_out} g={g} g_out={g_out}")
+    case = workloads.make_linear_case((297, T, d_in, d_out, g), T, d_in, d_out, g, None, g_out=g_out)
+    dY, W, m = dev_bf16(case.dY), dev_bf16(case.W), dev_f32(case.mask)
+    ws = workspace(gm.gm_workspace_size(gm.GM_OP_BWD, T, d_in, d_out, g, g_out))
+    ws.fill_(fill)
+    dX = empty_bf16(T, d_in)
+    gm.gm_masked_linear_bwd(dY, dev_bf16(case.X), W, m, g, dX, None, ws, g_out=g_out)
+    sync()
+    ref, b = ref_dx(oracle.from_bf16(case.dY), oracle.from_bf16(case.W), case.mask, g, g_out)
+    assert_close("dX", host_f64_from_bf16(dX), ref, bound=b)
+
+
 @pytest.mark.parametrize("T,d_in,d_out,g,g_out", [
     (1, 64, 8, 64, 1),          # 256 x 64 tiles, one slice: the second K group has none
     (33, 192, 72, 64, 1),       # a row past the first tile, columns past 128
