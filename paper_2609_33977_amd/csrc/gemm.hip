@@ -346,10 +346,10 @@ __global__ __launch_bounds__(64 * kFwdWaves) void fwd_kernel(const uint16_t* __r
     for (int j = 0; j < CA; ++j) {
       const int gr = group_of(v_cur, j);
       const uint32_t dead = ((~bits_cur[j] >> (gr & 31)) & 1u) << 31;
-      if constexpr (PACKED)
-        curA[j] = live ? group_voffset(uint32_t(piece_of(bits_cur[j], base_cur[j], gr)) * uint32_t(2 * G) +
-                                           uint32_t(sub * kBK * 2) + offA[j], j) | dead
-                       : kOOB;
+      if constexpr (PACKED)  // (rows past d_out have no base: their offsets are replaced, not flagged)
+        curA[j] = live && !dead ? group_voffset(uint32_t(piece_of(bits_cur[j], base_cur[j], gr)) * uint32_t(2 * G) +
+                                                    uint32_t(sub * kBK * 2) + offA[j], j)
+                                : kOOB;
       else
         curA[j] = offA[j] | dead;
     }
