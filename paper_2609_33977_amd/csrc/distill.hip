@@ -373,7 +373,7 @@ template <int BM, int BN, int KS>
 __global__ __launch_bounds__(64 * kLmWaves) void lmhead_bwd_kernel(const uint16_t* __restrict__ dz, int ldv,
                                                                   const uint16_t* __restrict__ W, int N, int d,
                                                                   int V, uint16_t* __restrict__ dH) {
-  wt_gemm<0, BM, BN, KS>(dz, ldv, W, V, d, N, nullptr, dH);
+  wt_gemm<BM, BN, KS>(dz, ldv, W, V, d, N, dH);
 }
 
 // ---------------------------------------------------------------- launchers

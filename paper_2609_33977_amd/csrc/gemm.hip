@@ -929,15 +929,16 @@ __global__ __launch_bounds__(64 * dx_waves(BM, KS)) void dx_kernel(const uint16_
                                              lane, dX, d_in, n0, T, m0, d_in);
 }
 
-// dX of small square groups over every row: a list column of 64 input columns
-// (four or two groups) keeps 94 % or 75 % of the rows at half the groups kept,
-// so gathering rows saves little, and its 64-column tiles move 1.9 times the
-// operand bytes per MFMA of a 256-column tile.
+// dX of small square groups over the mask rows that keep something in the
+// tile's columns: a list column of 64 input columns (four or two groups) keeps
+// 94 % or 75 % of the rows at half the groups kept, so gathering single rows saves
+// little, and its 64-column tiles move 1.9 times the operand bytes per MFMA of a
+// 256-column tile.
 template <int G, int BM, int BN, int KS>
 __global__ __launch_bounds__(512) void dx_dense_kernel(const uint16_t* __restrict__ dY, const uint16_t* __restrict__ W,
                                                        const float* __restrict__ mask, int T, int d_in, int d_out,
                                                        uint16_t* __restrict__ dX) {
-  wt_gemm<G, BM, BN, KS>(dY, d_out, W, d_out, d_in, T, mask, dX);
+  wt_gemm_masked<G, BM, BN, KS>(dY, d_out, W, d_out, d_in, T, mask, dX);
 }
 
 // ============================================================================ dY^T
