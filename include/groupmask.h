@@ -170,6 +170,8 @@ gm_status gm_workspace_size(int op, int64_t T, int64_t d_in, int64_t d_out, int3
  * A group with mask == 0 is skipped (its weights are never read); any other
  * value scales the group (1.0 for a hard selector).  bf16 inputs, fp32
  * accumulation, Y rounded to bf16 (round to nearest even).
+ * (A non-finite X[t, i] of a pruned group may still make Y[t, o] NaN, as 0 * X
+ * does in the formula.)
  *   X    [T, d_in]  bf16       W [d_out, d_in] bf16
  *   mask [d_out / g_out, d_in / g] fp32
  *   Y    [T, d_out] bf16, written in full
@@ -195,6 +197,9 @@ gm_status gm_masked_linear_fwd(const uint16_t* X, const uint16_t* W, const float
  * (Sec. 2.2 STE, Sec. 2.4 frozen weights):
  *   dX = dY (W (.) expand(mask))                       [T, d_in]   bf16
  *   dgate[u, v] = sum_{(o, i) in group (u, v)} W[o, i] (dY^T X)[o, i]   [G_out, G_in] fp32
+ * A pruned group adds nothing to dX, whatever dY holds (infinities and NaN
+ * included), except that 16 x 16 and 32 x 32 groups with more than 2048 mask
+ * rows may take 0 * dY of a row that keeps another group of the same 64 columns.
  * dgate is produced for every group, kept or pruned, and does not depend on
  * the mask; the weight gradient is never formed.  Either output may be NULL to
  * skip it (both NULL is a no-op); mask may be NULL only when dX is NULL.

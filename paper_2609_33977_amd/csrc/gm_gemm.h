@@ -206,6 +206,18 @@ __device__ __forceinline__ void gemm_mainloop(u32x4 (*As)[ABUF], u32x4 (*Bs)[BBU
   acc_drain<kAgprRows<MB> * NB>(reinterpret_cast<f32x4(&)[MB * NB]>(acc));
 }
 
+// Whether an accumulator of this lane is NaN (two compared at a time).
+template <int MB, int NB>
+__device__ __forceinline__ bool any_nan(const f32x4 (&acc)[MB][NB]) {
+  bool nan = false;
+#pragma unroll
+  for (int mb = 0; mb < MB; ++mb)
+#pragma unroll
+    for (int nb = 0; nb < NB; ++nb)
+      nan |= __builtin_isunordered(acc[mb][nb][0], acc[mb][nb][1]) | __builtin_isunordered(acc[mb][nb][2], acc[mb][nb][3]);
+  return nan;
+}
+
 // Epilogue of a K-loop tile of BM (m) x 256 (n) accumulators, waves 2 (m) x
 // NW/2 (n): out[r0 + n][c0 + m] = bf16(C[m][n]) for r0 + n < rlim (c0 + BM <=
 // clim or whole 8-column chunks below clim).  The bf16 tile goes through LDS

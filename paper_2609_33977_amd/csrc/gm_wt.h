@@ -66,6 +66,38 @@ __device__ __forceinline__ bool wt_mask(const float* __restrict__ mask, int G_ou
   return soft;
 }
 
+// The outputs of a tile that came out NaN, from the kept groups alone: a
+// pruned group's zeros times a non-finite B would make every output that
+// shares its K slices NaN.
+template <int G, int BM, int BN>
+__device__ __forceinline__ void wt_kept_only(const uint16_t* __restrict__ B, int ldb, const uint16_t* __restrict__ W, int K,
+                                          int d, int N, const float* __restrict__ mask, uint16_t* out,
+                                          const uint16_t* bits, int m0, int n0) {
+  __threadfence();  // the tile's stores
+  __syncthreads();
+  int e0 = threadIdx.x;  // opaque: nothing here is computed (and kept in registers) before the K-loop
+  asm volatile("" : "+v"(e0));
+  for (int e = e0; e < BM * BN; e += 512) {
+    const int j = m0 + e % BM, t = n0 + e / BM;
+    if (j >= d || t >= N) continue;
+    uint16_t* o = out + int64_t(t) * d + j;
+    if ((*reinterpret_cast<volatile uint16_t*>(o) & 0x7fffu) <= 0x7f80u) continue;
+    float a = 0.0f;
+    for (int u = 0; u < K / G; ++u) {
+      if (!(bits[u] >> (e % BM / 16) & 1)) continue;
+      const float m = mask[int64_t(u) * (d / G) + j / G];
+#pragma unroll
+      for (int q = 0; q < G; ++q) {
+        const int k = u * G + q;
+        float w = bf16_to_f32(W[int64_t(k) * d + j]);
+        if (m != 1.0f) w = bf16_to_f32(uint16_t(f32_to_bf16_bits(m * w)));
+        a += bf16_to_f32(B[int64_t(t) * ldb + k]) * w;
+      }
+    }
+    *o = uint16_t(f32_to_bf16_bits(a));
+  }
+}
+
 // Tile BM (j) x BN (t) on eight waves: KS wave groups of 2 (j) x NW/KS/2 (t)
 // waves split the K slices (contiguous shares, the last padded with zero
 // slices).  W' tiles are MN-major (transposing reads), B tiles K-major.
@@ -191,8 +223,8 @@ __device__ __forceinline__ void wt_tile(const uint16_t* __restrict__ B, int ldb,
     const i32x4_t rM = make_rsrc(mask, uint32_t(G_out) * uint32_t(G_in) * 4u);
     const uint32_t ldsM = lds_addr(s_msoft) + uint32_t(wave) * 256u;
     auto prepare_soft = [&](int st) {
-      int el = lane;  // opaque: nothing is computed from it (and kept in registers) before the K-loop
-      asm volatile("" : "+v"(el));
+      int el = lane;  // opaque in the largest tile: nothing is computed from it (and kept in registers) before the K-loop
+      if constexpr (CA > 2) asm volatile("" : "+v"(el));
       const int u = WALK ? (el < GT ? u0 : u1) : (st + s0) * MR + el / GT, v = m0 / GG + el % GT;
       const bool ok = st < ng && el < GT * MR && u >= 0 && u < G_out && v < G_in;
       dma4_buf(rM, ok ? (uint32_t(u) * uint32_t(G_in) + uint32_t(v)) * 4u : kOOB,
@@ -202,7 +234,7 @@ __device__ __forceinline__ void wt_tile(const uint16_t* __restrict__ B, int ldb,
     auto rescale = [&](int st) {
       const float* ms = s_msoft + (st % STAGES) * 64 * NW + 64 * wave;
       uint32_t va = vA;  // opaque, as above
-      asm volatile("" : "+v"(va));
+      if constexpr (CA > 2) asm volatile("" : "+v"(va));
       u32x4* p = As[st % STAGES] + wg * CA * 64 + lane;
 #pragma unroll
       for (int h = 0; h < CA; h += HS) {
@@ -227,6 +259,8 @@ __device__ __forceinline__ void wt_tile(const uint16_t* __restrict__ B, int ldb,
   }
   int et = tid, el = lane;  // opaque: the epilogue's addresses are not computed (and kept in registers) before the K-loop
   asm volatile("" : "+v"(et), "+v"(el));
+  bool nan = false;
+  if constexpr (G > 0) nan = __syncthreads_or(any_nan(acc));
   if constexpr (KS == 1)
     store_tile_rows<BM, MB, NB, NW>(acc, reinterpret_cast<char*>(smem), reinterpret_cast<char*>(smem + STAGES * BM * 4),
                                     wm, wn, et, el, out, d, n0, N, m0, d);
@@ -234,6 +268,8 @@ __device__ __forceinline__ void wt_tile(const uint16_t* __restrict__ B, int ldb,
     store_tile_ksum2<BM, BN, MB, NB, NW, HC>(acc, reinterpret_cast<f32x4*>(smem),
                                              reinterpret_cast<char*>(smem) + NW * HC * NB * 1024, kg, wg, wm, wn, et,
                                              el, out, d, n0, N, m0, d);
+  if constexpr (G > 0)
+    if (nan) wt_kept_only<G, BM, BN>(B, ldb, W, K, d, N, mask, out, sm->bits, m0, n0);
 }
 
 // Every row of W'.

@@ -80,3 +80,32 @@ def test_dx_time_falls_with_the_density(g):
     sparse, half = best((u < 0.03).float()), best((u < 0.5).float())
     say(f"  3 % kept {100 * sparse:.1f} us, half kept {100 * half:.1f} us")
     assert sparse < 0.8 * half
+
+
+@pytest.mark.parametrize("kept", [0.08, 0.6])
+@pytest.mark.parametrize("T,d_in,d_out,g", [(140, 320, 336, 16), (257, 576, 1056, 32), (2041, 4096, 800, 32),
+                                            (4090, 4096, 272, 16)])
+def test_dx_of_pruned_groups_ignores_non_finite_dy(T, d_in, d_out, g, kept):
+    # an infinite or NaN dY[t, o] reaches dX[t, i] only through a kept group of (o, i)
+    import paper_2609_33977_amd as gm
+    say(f"sparse dX, non-finite dY: T={T} d_in={d_in} d_out={d_out} g={g} kept={kept}")
+    case = workloads.make_linear_case((302, T, d_in, d_out, g), T, d_in, d_out, g, None, g_out=g)
+    r = workloads.gen.rng_for(303, T, g)
+    m = (r.uniform(size=case.mask.shape) < kept).astype(np.float32)
+    m[m.shape[0] // 2] = 0.0  # a mask row that keeps nothing
+    m[1, 0] = 0.75
+    bad = {(3, d_out // 2): 0x7F80, (T - 1, 5): 0xFF80, (T // 2, d_out - 1): 0x7FC0}
+    dY, hit = case.dY.copy(), np.zeros((T, d_in), dtype=bool)
+    clean = case.dY.copy()
+    for (t, o), bits in bad.items():
+        dY[t, o], clean[t, o] = bits, 0
+        hit[t] |= np.repeat(m[o // g] != 0, g)
+    dX = empty_bf16(T, d_in)
+    ws = workspace(gm.gm_workspace_size(gm.GM_OP_BWD, T, d_in, d_out, g, g))
+    gm.gm_masked_linear_bwd(dev_bf16(dY), dev_bf16(case.X), dev_bf16(case.W), dev_f32(m), g, dX, None, ws, g_out=g)
+    sync()
+    got = host_f64_from_bf16(dX)
+    assert not np.any(np.isfinite(got[hit])), "a kept group's infinity or NaN is lost"
+    ref, b = ref_dx(oracle.from_bf16(clean), oracle.from_bf16(case.W), m, g, g)
+    got[hit], ref[hit] = 0.0, 0.0
+    assert_close("dX", got, ref, bound=b)
