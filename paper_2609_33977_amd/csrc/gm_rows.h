@@ -40,7 +40,7 @@ __device__ __forceinline__ void wave_sums(float (&acc)[TB]) {
 }
 
 // acc[t] = sum over pieces p0 .. p0 + nk - 1 of scale * (piece . X[t0 + t, its columns]), t < ntok <= TB, in fp32
-// (pieces in any order; columns past d_in are skipped).
+// (pieces in any order; those with a column past d_in add nothing).
 template <int TB>
 __device__ __forceinline__ void packed_row(const uint16_t* __restrict__ X, const uint16_t* __restrict__ Wp,
                                            const int* __restrict__ chunk, const float* __restrict__ scale, int64_t p0,
@@ -53,30 +53,29 @@ __device__ __forceinline__ void packed_row(const uint16_t* __restrict__ X, const
 #pragma unroll
   for (int t = 0; t < TB; ++t) acc[t] = 0.0f;
   for (int k0 = 0; k0 < nk; k0 += 2 * gps) {
-    int v[2];
-    float m[2];
-    u32x4 w[2];
-#pragma unroll
-    for (int q = 0; q < 2; ++q) {
-      const int k = k0 + q * gps + slot;
-      v[q] = k < nk ? chunk[p0 + k] : -1;
-      m[q] = 0.0f;
-      w[q] = zero16();
-      if (v[q] >= 0 && v[q] < G_in) {
-        m[q] = scale[p0 + k];
-        w[q] = ld16(Wp + (p0 + k) * g + e);
-      } else {
-        v[q] = -1;
-      }
+    const int ka = k0 + slot, kb = k0 + gps + slot;
+    int va = 0, vb = 0;
+    float ma = 0.0f, mb = 0.0f;
+    u32x4 wa = zero16(), wb = zero16();
+    if (ka < nk) {  // the weights do not wait for the column
+      va = chunk[p0 + ka];
+      ma = scale[p0 + ka];
+      wa = ld16(Wp + (p0 + ka) * g + e);
     }
+    if (kb < nk) {
+      vb = chunk[p0 + kb];
+      mb = scale[p0 + kb];
+      wb = ld16(Wp + (p0 + kb) * g + e);
+    }
+    if (uint32_t(va) >= uint32_t(G_in)) va = 0, ma = 0.0f;
+    if (uint32_t(vb) >= uint32_t(G_in)) vb = 0, mb = 0.0f;
 #pragma unroll
     for (int t = 0; t < TB; ++t) {
       if (t < ntok) {
         const uint16_t* xr = X + int64_t(t0 + t) * d_in + e;
         float p = 0.0f;
-#pragma unroll
-        for (int q = 0; q < 2; ++q)
-          if (v[q] >= 0) p += m[q] * dot8_bf16(w[q], ld16(xr + int64_t(v[q]) * g));
+        if (ka < nk) p += ma * dot8_bf16(wa, ld16(xr + int64_t(va) * g));
+        if (kb < nk) p += mb * dot8_bf16(wb, ld16(xr + int64_t(vb) * g));
         acc[t] += p;
       }
     }
