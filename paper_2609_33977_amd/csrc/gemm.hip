@@ -79,9 +79,9 @@ constexpr int kFwdRowsAfter = 4, kDgateRowsAfter = 4, kDxRowsAfter = 1;
 // selectors.  The piece of (row, group) is the row's first piece plus the
 // number of kept groups before it, from the tile's kept bits (built in the
 // prologue from chunk[]) and a running count per 32-bit word.  A tile with a
-// fractional selector (which this path would round into bf16 weights) or with
-// pieces out of column order computes its rows one wave at a time in fp32
-// (packed_row).
+// fractional selector (which this K-loop would round into bf16 weights) multiplies
+// each slice's products by it in fp32 instead; a tile with pieces out of column
+// order computes its rows piece by piece (packed_row).
 struct PackedArgs {
   const int *chunk, *rowptr;
   const float* scale;
@@ -164,7 +164,7 @@ __global__ __launch_bounds__(64 * kFwdWaves) void fwd_kernel(const uint16_t* __r
     const int rp0 = r < rows ? pk.rowptr[m0 + r] : 0, rp1 = r < rows ? pk.rowptr[m0 + r + 1] : 0;
     for (int e = tid; e < RB * words; e += 64 * NW) s_bits[e % RB][e / RB] = 0;
     __syncthreads();
-    bool odd = false;
+    bool odd = false, soft = false;
     for (int e = rp0 + tid % TPR; e < rp1; e += TPR * LP) {
       int v[LP], before[LP];
       float m[LP];
@@ -177,23 +177,15 @@ __global__ __launch_bounds__(64 * kFwdWaves) void fwd_kernel(const uint16_t* __r
       }
 #pragma unroll
       for (int i = 0; i < LP; ++i) {
-        const bool in = e + i * TPR < rp1, ok = v[i] > before[i] && v[i] < G_in && m[i] == 1.0f;
+        const bool in = e + i * TPR < rp1, ok = v[i] > before[i] && v[i] < G_in;
         if (in && ok) atomicOr(&s_bits[r][v[i] >> 5], 1u << (v[i] & 31));
         odd |= in && !ok;
+        soft |= m[i] != 1.0f;
       }
     }
+    if (soft) s_soft = 1;
     if (__syncthreads_or(odd)) {
-      for (int o = m0 + wave; o < m0 + rows; o += NW) {
-        const int p = pk.rowptr[o], nk = pk.rowptr[o + 1] - p;
-        for (int t0 = n0; t0 < min(n0 + BN, T); t0 += 16) {
-          const int ntok = min(16, min(n0 + BN, T) - t0);
-          float sum[16];
-          packed_row<16>(X, W, pk.chunk, pk.scale, p, nk, t0, ntok, d_in, G, lane, sum);
-#pragma unroll
-          for (int t = 0; t < 16; ++t)
-            if (lane == 0 && t < ntok) Y[int64_t(t0 + t) * d_out + o] = uint16_t(f32_to_bf16_bits(sum[t]));
-        }
-      }
+      packed_rows(X, W, pk.chunk, pk.scale, pk.rowptr, m0 + wave, m0 + rows, NW, n0, min(n0 + BN, T), d_in, d_out, G, lane, Y);
       return;
     }
     if (tid % TPR == 0 && r < rows) {
@@ -379,7 +371,7 @@ __global__ __launch_bounds__(64 * kFwdWaves) void fwd_kernel(const uint16_t* __r
   // in, with no extra wait.
   constexpr int RW = 16 * CA;
   static_assert(RW == 32 || (RW == 64 && UG == 1), "one lane per (row of the wave, group of the unit)");
-  __shared__ float s_msoft[PACKED ? 1 : STAGES][64 * NW];
+  __shared__ float s_msoft[STAGES][64 * NW];
   const i32x4_t rM = make_rsrc(mask, uint32_t(d_out / GO) * uint32_t(G_in) * 4u);
   const uint32_t ldsM = lds_addr(s_msoft) + uint32_t(wave) * 256u;
   auto prepare_soft = [&](int st) {
@@ -390,7 +382,7 @@ __global__ __launch_bounds__(64 * kFwdWaves) void fwd_kernel(const uint16_t* __r
     prepare(st);
   };
   auto rescale = [&](int st) {
-    const float* ms = s_msoft[PACKED ? 0 : st % STAGES] + 64 * wave;
+    const float* ms = s_msoft[st % STAGES] + 64 * wave;
     u32x4* A = As[kg * STAGES + st % STAGES];
     float m[CA];
     u32x4 w[CA];  // read beside the selectors: one LDS round trip before the barrier, not two
@@ -411,7 +403,55 @@ __global__ __launch_bounds__(64 * kFwdWaves) void fwd_kernel(const uint16_t* __r
   f32x4 acc[MB][NB];
   u32x4(*Ag)[BM * 4] = As + kg * STAGES;
   u32x4(*Bg)[BN * 4] = Bs + kg * STAGES;
-  if (!PACKED && s_soft)
+  if (PACKED && s_soft) {
+    // Packed, fractional selectors: the K-loop without its interleaving (one
+    // barrier per slice); each slice's products start from zero and enter the
+    // sums times the rows' selectors, in fp32.  4096 x 4096 half kept, T = 128 /
+    // 512: 81 / 82 us, 40 / 43 with binary selectors; computing the tile's rows one
+    // wave at a time took 1850 us, one wave per row of the whole matrix 205 / 790.
+    if constexpr (PACKED) {
+      typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
+      const i32x4_t rS = make_rsrc(pk.scale + p0, uint32_t(np) * 4u);
+      auto start = [&](int st) {  // the copies of slice st and of its selectors
+        const int rr = RW * wg + (lane & (RW - 1)), h = lane / RW, gr = v_cur * UG + (UG == 2 ? h : 0);
+        const uint32_t b = s_bits[rr][gr >> 5];
+        const bool ok = st < ng && ((b >> (gr & 31)) & 1u) && (UG == 2 || h == 0);
+        dma4_buf(rS, ok ? uint32_t(piece_of(b, s_base[rr][gr >> 5], gr)) * 4u : kOOB, ldsM + uint32_t(st % STAGES) * (64u * NW * 4u));
+        prepare(st);
+#pragma unroll
+        for (int p = 0; p < PER_STAGE; ++p) issue(st, p);
+      };
+#pragma unroll
+      for (int mb = 0; mb < MB; ++mb)
+#pragma unroll
+        for (int nb = 0; nb < NB; ++nb) acc[mb][nb] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+      for (int st = 0; st < (nst ? STAGES - 1 : 0); ++st) start(st);
+      for (int kt = 0; kt < nst; ++kt) {
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");  // this wave's reads of slice kt - 1 are done
+        wait_vmcnt<(PER_STAGE + 1) * (STAGES - 2)>();        // ... and its copies of slice kt
+        block_sync();
+        start(kt + STAGES - 1);  // into the buffer of slice kt - 1
+        u32x4 bf[NB];
+        load_bfrags<NB, true, 0>(Bg[kt % STAGES], wn * NB * 16, lane, bf);
+#pragma unroll
+        for (int mb = 0; mb < MB; ++mb) {
+          const u32x4 af = km_frag(Ag[kt % STAGES], (wm * MB + mb) * 16, lane);
+          const int row = (wm * MB + mb) * 16 + 4 * (lane >> 4);  // of this lane's four results
+#pragma unroll
+          for (int h = 0; h < UG; ++h) {
+            const f32x4 m = *reinterpret_cast<const f32x4*>(&s_msoft[kt % STAGES][(kg * NG + row / RW) * 64 + row % RW + 32 * h]);
+            const u32x4 ah = UG == 1 || lane >> 5 == h ? af : zero16();
+#pragma unroll
+            for (int nb = 0; nb < NB; ++nb)
+              acc[mb][nb] += m * __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+                                     __builtin_bit_cast(bf16x8_t, ah), __builtin_bit_cast(bf16x8_t, bf[nb]),
+                                     f32x4{0.0f, 0.0f, 0.0f, 0.0f}, 0, 0, 0);
+          }
+        }
+      }
+      wait_vmcnt<0>();  // zero-fill copies of slices past the end
+    }
+  } else if (!PACKED && s_soft)
     gemm_mainloop<MB, NB, true, true, 0, 0, PER_STAGE, STAGES, RA, 1>(
         Ag, Bg, nst, wm * MB * 16, wn * NB * 16, lane, acc, prepare_soft, issue, rescale,
         [](int, const u32x4(&)[NB]) {}, live);

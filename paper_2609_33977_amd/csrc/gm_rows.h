@@ -83,4 +83,22 @@ __device__ __forceinline__ void packed_row(const uint16_t* __restrict__ X, const
   wave_sums(acc);
 }
 
+// Tokens [t0, t1) of rows o, o + step, ... below o1 of Y on one wave.
+__device__ __forceinline__ void packed_rows(const uint16_t* __restrict__ X, const uint16_t* __restrict__ Wp,
+                                            const int* __restrict__ chunk, const float* __restrict__ scale,
+                                            const int* __restrict__ rowptr, int o, int o1, int step, int t0, int t1,
+                                            int d_in, int d_out, int g, int lane, uint16_t* __restrict__ Y) {
+  for (; o < o1; o += step) {
+    const int p = rowptr[o], nk = rowptr[o + 1] - p;
+    for (int t = t0; t < t1; t += 16) {
+      const int ntok = min(16, t1 - t);
+      float sum[16];
+      packed_row<16>(X, Wp, chunk, scale, p, nk, t, ntok, d_in, g, lane, sum);
+#pragma unroll
+      for (int q = 0; q < 16; ++q)
+        if (lane == 0 && q < ntok) Y[int64_t(t + q) * d_out + o] = uint16_t(f32_to_bf16_bits(sum[q]));
+    }
+  }
+}
+
 }  // namespace gm
