@@ -256,8 +256,9 @@ gm_status gm_pack_rows(const uint16_t* W, const float* mask, int64_t d_in, int64
  * gm_packed_linear_fwd -- forward of a pruned linear from its packed export
  * (the inference path of the pruned model): the same Y as gm_masked_linear_fwd
  * with the mask that gm_pack_rows consumed, for any T >= 1: up to 16 tokens read
- * every kept weight once; more run the GEMM on the pieces, in which fractional
- * selectors stay in fp32 (tiles that hold one take about twice as long).
+ * every kept weight once; some more run in passes of 16, and many the GEMM on the
+ * pieces (fractional selectors stay in fp32 in both; GEMM tiles that hold one
+ * take about twice as long).
  *   X [T, d_in] bf16; Wp, chunk, scale, rowptr as written by gm_pack_rows,
  *   which must have held every kept group (rowptr[d_out] <= its capacity);
  *   g is the width of the exported pieces (the group width; a square export

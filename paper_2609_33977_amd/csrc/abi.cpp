@@ -143,6 +143,7 @@ size_t fwd_workspace(int64_t T, int64_t d_in, int64_t d_out, int32_t g) {
 struct FwdPlan {
   gm::FwdTile tile;
   int ks;
+  int64_t ns;  // estimated time
 };
 
 bool fwd_tile_fits(gm::FwdTile tile, int64_t d_in, int32_t g, int32_t g_out, bool packed) {
@@ -158,21 +159,16 @@ FwdPlan fwd_plan(int64_t T, int64_t d_in, int64_t d_out, int32_t g, int32_t g_ou
   const int64_t slices = d_in / 32;
   auto tiles = [&](int64_t bm, int64_t bn) { return ((d_out + bm - 1) / bm) * ((T + bn - 1) / bn); };
   auto reduce_ns = [&](int64_t k, int64_t rate) { return 4000 + k * T * d_out * 8 / rate; };  // rate: bytes per ns
-  FwdPlan best{FwdTile::k128x128, 1};
-  int64_t best_ns = gm::rounds_ns(tiles(128, 128), 9000 + 250 * slices);
-  for (int k = 2; k <= ks; ++k) {  // ks: what the workspace holds
-    const int64_t ns = gm::rounds_ns(tiles(128, 128) * k, 9000 + 250 * slices / k) + reduce_ns(k, 8000);
-    if (ns < best_ns) best = {FwdTile::k128x128, k}, best_ns = ns;
-  }
-  if (fwd_tile_fits(FwdTile::k256x128, d_in, g, g_out, packed)) {
-    const int64_t ns = gm::rounds_ns(tiles(256, 128), 14000 + 420 * slices);
-    if (ns < best_ns) best = {FwdTile::k256x128, 1}, best_ns = ns;
-  }
-  if (fwd_tile_fits(FwdTile::k256x256, d_in, g, g_out, packed)) {
-    int64_t ns = gm::rounds_ns(tiles(256, 256) * ks, 15000 + 660 * slices / ks);
-    if (ks > 1) ns += reduce_ns(ks, 15000);
-    if (ns < best_ns) best = {FwdTile::k256x256, ks}, best_ns = ns;
-  }
+  FwdPlan best{FwdTile::k128x128, 1, gm::rounds_ns(tiles(128, 128), 9000 + 250 * slices)};
+  auto consider = [&](FwdTile tile, int k, int64_t ns) {
+    if (ns < best.ns) best = {tile, k, ns};
+  };
+  for (int k = 2; k <= ks; ++k)  // ks: what the workspace holds
+    consider(FwdTile::k128x128, k, gm::rounds_ns(tiles(128, 128) * k, 9000 + 250 * slices / k) + reduce_ns(k, 8000));
+  if (fwd_tile_fits(FwdTile::k256x128, d_in, g, g_out, packed))
+    consider(FwdTile::k256x128, 1, gm::rounds_ns(tiles(256, 128), 14000 + 420 * slices));
+  if (fwd_tile_fits(FwdTile::k256x256, d_in, g, g_out, packed))
+    consider(FwdTile::k256x256, ks, gm::rounds_ns(tiles(256, 256) * ks, 15000 + 660 * slices / ks) + (ks > 1 ? reduce_ns(ks, 15000) : 0));
   return best;
 }
 
@@ -558,8 +554,9 @@ GM_EXPORT gm_status gm_packed_linear_fwd(const uint16_t* X, const uint16_t* Wp, 
   if (gm_status st = check_device()) return st;
   if (T > kDecodeTokens) {
     const FwdPlan p = fwd_plan(T, d_in, d_out, g, 1, true, 1);
-    return from_hip(gm::launch_fwd_packed(X, Wp, chunk, scale, rowptr, int(T), int(d_in), int(d_out), g, Y, p.tile,
-                                          stream));
+    if (!gm::packed_passes(T, d_in, d_out, g, p.ns))
+      return from_hip(gm::launch_fwd_packed(X, Wp, chunk, scale, rowptr, int(T), int(d_in), int(d_out), g, Y, p.tile,
+                                            stream));
   }
   return from_hip(
       gm::launch_gemv_packed(X, Wp, chunk, scale, rowptr, int(T), int(d_in), int(d_out), g, Y, stream));

@@ -148,7 +148,6 @@ __device__ __forceinline__ u32x4 ld16_rsrc(__amdgpu_buffer_rsrc_t r, uint32_t of
 // every token count and for 32-row blocks at 16 tokens (2-5 %), but 2-4 %
 // slower for 32-row blocks at 2 and 8 tokens, which keep the direct loads.
 constexpr int kMmaWaves = 8;
-constexpr int kMmaMaskFloats = 8192;  // staged mask floats per block: mask rows of the block x selectors per row
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 
@@ -156,7 +155,12 @@ typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 // 64 rows, or more than 8 tokens, where it measured 2-5 % faster.
 // MF: floats of the staged tables.  With tables for kMmaMaskFloats the LDS of a
 // 32-row block (80 KiB and more) kept a second one off the CU.
-template <int RT, bool PACKED, bool XL, int MF>
+// PASSES: more than 16 tokens of the packed export, 16 per block; adjacent
+// blocks take the same rows.  Soft selectors stay in fp32 there: they multiply the
+// products of their slice, not the weights.  Rows whose pieces are not in
+// column order, and rows with a NaN (a pruned group's zeros times a non-finite
+// X), are computed piece by piece (packed_row).
+template <int RT, bool PACKED, bool XL, int MF, bool PASSES = false>
 __global__ __launch_bounds__(64 * kMmaWaves) void gemv_mfma_kernel(const uint16_t* __restrict__ X,
                                                                   const uint16_t* __restrict__ W,
                                                                   const float* __restrict__ mask,
@@ -173,8 +177,16 @@ __global__ __launch_bounds__(64 * kMmaWaves) void gemv_mfma_kernel(const uint16_
   // Per wave: its partial tiles, after the K loop (XL: in the K loop, the X slices of one load batch).
   __shared__ u32x4 s_x[kMmaWaves][XL ? 4 * 64 : RT * 64];
   f32x4(*s_part)[XL ? 4 : RT][64] = reinterpret_cast<f32x4(*)[XL ? 4 : RT][64]>(s_x);
+  static_assert(PACKED || !PASSES, "passes read the packed export");
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int o0 = blockIdx.x * R;
+  const int passes = PASSES ? (T + 15) / 16 : 1;
+  const int o0 = int(blockIdx.x) / passes * R;
+  if constexpr (PASSES) {
+    const int t0 = int(blockIdx.x) % passes * 16;
+    X += int64_t(t0) * d_in;
+    Y += int64_t(t0) * d_out;
+    T = min(T - t0, 16);
+  }
   const int G_in = d_in / g;
   const int mrows = go == 1 ? R : (R > go ? R / go : 1);
   const int u0 = o0 / go;
@@ -188,7 +200,8 @@ __global__ __launch_bounds__(64 * kMmaWaves) void gemv_mfma_kernel(const uint16_
   // writes its selector scale[p] and its index into (row, chunk[p]); pieces
   // whose column is out of range are ignored.
   int soft_here = 0;
-  int p0 = 0;  // packed: first piece of the block
+  bool odd = false;  // PASSES: pieces out of column order
+  int p0 = 0;        // packed: first piece of the block
   if constexpr (PACKED) {
     for (int e = tid; e <= rows; e += NT) s_rp[e] = rowptr[o0 + e];
     for (int e = tid; e < R * G_in; e += NT) s_m[e] = 0.0f;
@@ -208,6 +221,7 @@ __global__ __launch_bounds__(64 * kMmaWaves) void gemv_mfma_kernel(const uint16_
         s_idx[lo * G_in + v] = e;
         soft_here |= sv != 0.0f && sv != 1.0f;
       }
+      if constexpr (PASSES) odd |= p0 + e > s_rp[lo] && chunk[p0 + e - 1] >= v;
     }
   } else {
     for (int e = tid; e < mrows * G_in; e += NT) {
@@ -218,6 +232,14 @@ __global__ __launch_bounds__(64 * kMmaWaves) void gemv_mfma_kernel(const uint16_
     }
   }
   const bool soft = __syncthreads_or(soft_here);
+  auto piece_by_piece = [&] {
+    packed_rows(X, W, chunk, scale, rowptr, o0 + wave, o0 + rows, kMmaWaves, 0, T, d_in, d_out, g, lane, Y);
+  };
+  if constexpr (PASSES)
+    if (__syncthreads_or(odd)) {
+      piece_by_piece();
+      return;
+    }
 
   const int r = lane & 15, kc = lane >> 4;
   // W is loaded with four adjacent lanes per 64-byte row segment (row rl,
@@ -323,13 +345,27 @@ __global__ __launch_bounds__(64 * kMmaWaves) void gemv_mfma_kernel(const uint16_
         for (int rt = 0; rt < RT; ++rt) {
           const float mq = m[rt][q];
           u32x4 aq = av[rt][q];
-          if constexpr (decltype(soft_tag)::value) aq = scale_bf16x8(aq, mq);
+          if constexpr (decltype(soft_tag)::value && !PASSES) aq = scale_bf16x8(aq, mq);
           aq = u32x4{uint32_t(__builtin_amdgcn_ds_bpermute(bpa, int(aq.x))),
                      uint32_t(__builtin_amdgcn_ds_bpermute(bpa, int(aq.y))),
                      uint32_t(__builtin_amdgcn_ds_bpermute(bpa, int(aq.z))),
                      uint32_t(__builtin_amdgcn_ds_bpermute(bpa, int(aq.w)))};
-          acc[rt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, aq),
-                                                            __builtin_bit_cast(bf16x8, bv[q]), acc[rt], 0, 0, 0);
+          if constexpr (decltype(soft_tag)::value && PASSES) {
+            // the slice's groups (two 16-wide ones: one half of K at a time), each times its four rows' selectors
+            if (sb + q >= s1) continue;
+            const int halves = g == 16 ? 2 : 1;
+            for (int h = 0; h < halves; ++h) {
+              const u32x4 ah = halves == 1 || (kc >> 1) == h ? aq : zero16();
+              const f32x4 p = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+                  __builtin_bit_cast(bf16x8, ah), __builtin_bit_cast(bf16x8, bv[q]), f32x4{0.0f, 0.0f, 0.0f, 0.0f}, 0, 0, 0);
+              const int at = (rt * 16 + 4 * kc) * G_in + (((sb + q) * 32 + 16 * h) >> lg);
+#pragma unroll
+              for (int i = 0; i < 4; ++i) acc[rt][i] += s_m[at + i * G_in] * p[i];
+            }
+          } else {
+            acc[rt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, aq),
+                                                              __builtin_bit_cast(bf16x8, bv[q]), acc[rt], 0, 0, 0);
+          }
         }
     }
   };
@@ -340,18 +376,23 @@ __global__ __launch_bounds__(64 * kMmaWaves) void gemv_mfma_kernel(const uint16_
 #pragma unroll
   for (int rt = 0; rt < RT; ++rt) s_part[wave][rt][lane] = acc[rt];
   __syncthreads();
+  f32x4 sum = {0.0f, 0.0f, 0.0f, 0.0f};
   if (wave < RT) {
-    const int rt = wave;
-    f32x4 sum = s_part[0][rt][lane];
+    sum = s_part[0][wave][lane];
 #pragma unroll
-    for (int w = 1; w < kMmaWaves; ++w) sum += s_part[w][rt][lane];
-    const int ob = o0 + rt * 16 + 4 * kc;
-    if (r < T && ob < d_out) {
-      uint2 v;
-      v.x = pack_bf16x2(sum[0], sum[1]);
-      v.y = pack_bf16x2(sum[2], sum[3]);
-      *reinterpret_cast<uint2*>(Y + int64_t(r) * d_out + ob) = v;
+    for (int w = 1; w < kMmaWaves; ++w) sum += s_part[w][wave][lane];
+  }
+  if constexpr (PASSES)
+    if (__syncthreads_or(__builtin_isunordered(sum[0], sum[1]) | __builtin_isunordered(sum[2], sum[3]))) {
+      piece_by_piece();
+      return;
     }
+  const int ob = o0 + wave * 16 + 4 * kc;
+  if (wave < RT && r < T && ob < d_out) {
+    uint2 v;
+    v.x = pack_bf16x2(sum[0], sum[1]);
+    v.y = pack_bf16x2(sum[2], sum[3]);
+    *reinterpret_cast<uint2*>(Y + int64_t(r) * d_out + ob) = v;
   }
 }
 
@@ -581,6 +622,25 @@ static bool launch_mfma(const uint16_t* X, const uint16_t* W, const float* mask,
   return true;
 }
 
+// False (nothing launched): the tables do not fit.
+static bool launch_passes(const uint16_t* X, const uint16_t* Wp, const int* chunk, const float* scale, const int* rowptr,
+                          int T, int d_in, int d_out, int g, uint16_t* Y, hipStream_t s, hipError_t& err) {
+  const int G_in = d_in / g, rows = passes_rows(T, d_in, d_out, g);
+  if (rows == 0) return false;
+  const dim3 grid(unsigned((T + 15) / 16 * ((d_out + rows - 1) / rows))), block(64 * kMmaWaves);
+#define GM_PASSES(RTV, MFV)                                                                                          \
+  hipLaunchKernelGGL((gemv_mfma_kernel<RTV, true, true, MFV, true>), grid, block, 0, s, X, Wp, nullptr, chunk, scale, \
+                     rowptr, T, d_in, d_out, g, 1, Y)
+  if (rows == 32) {
+    if (32 * G_in <= 4096) GM_PASSES(2, 4096); else GM_PASSES(2, kMmaMaskFloats);
+  } else {
+    if (16 * G_in <= 2048) GM_PASSES(1, 2048); else if (16 * G_in <= 4096) GM_PASSES(1, 4096); else GM_PASSES(1, kMmaMaskFloats);
+  }
+#undef GM_PASSES
+  err = hipGetLastError();
+  return true;
+}
+
 hipError_t launch_gemv_inplace(const uint16_t* X, const uint16_t* W, const float* mask, int T, int d_in, int d_out,
                                int g, int go, uint16_t* Y, hipStream_t s) {
   hipError_t err = hipSuccess;
@@ -598,6 +658,7 @@ hipError_t launch_gemv_packed(const uint16_t* X, const uint16_t* Wp, const int* 
                               const int* rowptr, int T, int d_in, int d_out, int g, uint16_t* Y, hipStream_t s) {
   if (T == 1) return launch_t1<true>(X, nullptr, nullptr, Wp, chunk, scale, rowptr, d_in, d_out, g, 1, Y, s);
   hipError_t err = hipSuccess;
+  if (T > 16 && launch_passes(X, Wp, chunk, scale, rowptr, T, d_in, d_out, g, Y, s, err)) return err;
   if (T <= 16 && launch_mfma<true>(X, Wp, nullptr, chunk, scale, rowptr, T, d_in, d_out, g, 1, Y, s, err)) return err;
   return gemv_passes<true, 1>(X, nullptr, nullptr, Wp, chunk, scale, rowptr, T, d_in, d_out, g, 1, Y, s);
 }

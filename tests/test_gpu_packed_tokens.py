@@ -113,3 +113,39 @@ def test_a_fractional_export_costs_little_more_than_a_binary_one(T):
     s = _best(lambda: gm.gm_packed_linear_fwd(X, *soft, d, g, Y))
     say(f"packed, T={T}: binary {100 * h:.1f} us, fractional {100 * s:.1f} us")
     assert s < 4.0 * h
+
+
+@pytest.mark.parametrize("T,d_in,d_out,g", [
+    (17, 512, 8, 512),
+    (32, 8256, 5120, 64),     # 129 groups per row: 16-row blocks
+    (47, 4096, 5128, 128),    # 32-row blocks, 8 rows past the last
+    (64, 1024, 1056, 32),
+    (33, 16384, 64, 32),      # 512 groups per row
+    (18, 5120, 4112, 16),     # 320 groups per row
+])
+def test_packed_passes_of_16_tokens(T, d_in, d_out, g):
+    import paper_2609_33977_amd as gm
+    say(f"packed passes: T={T} d_in={d_in} d_out={d_out} g={g}")
+    g_out = g if g < 64 else 1
+    case = workloads.make_linear_case((312, T, d_in, d_out, g), T, d_in, d_out, g, None, g_out=g_out)
+    mask = case.mask.astype(np.float32).copy()
+    mask[0], mask[-1, 1:] = 0.0, 0.0
+    X, m = dev_bf16(case.X), dev_f32(mask)
+    packed = _pack(dev_bf16(case.W), m, g, g_out)
+    Y = empty_bf16(T, d_out)
+    gm.gm_packed_linear_fwd(X, *packed, d_out, g, Y)
+    sync()
+    Xo, Wo = oracle.from_bf16(case.X), oracle.from_bf16(case.W)
+    ref = oracle.linear_fwd(Xo, Wo, mask, g, g_out)
+    assert_close("Y", host_f64_from_bf16(Y), ref, bound=_bound(Xo, Wo, mask, g, g_out, ref))
+
+
+def test_one_token_more_than_16_costs_little():
+    # 10 us both, with the calls' own time (12 and 14 us for the kernels); 44 us in the GEMM's eight 128 x 128 tiles
+    import paper_2609_33977_amd as gm
+    d_out, d_in, g = 1024, 4096, 64
+    X, packed, Y = _layer(17, d_out, d_in, g, False)
+    a = _best(lambda: gm.gm_packed_linear_fwd(X[:16], *packed, d_out, g, Y[:16]))
+    b = _best(lambda: gm.gm_packed_linear_fwd(X, *packed, d_out, g, Y))
+    say(f"packed {d_out} x {d_in}: 16 tokens {100 * a:.1f} us, 17 tokens {100 * b:.1f} us")
+    assert b < 3.0 * a
