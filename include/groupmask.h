@@ -259,6 +259,8 @@ gm_status gm_pack_rows(const uint16_t* W, const float* mask, int64_t d_in, int64
  * every kept weight once; some more run in passes of 16, and many the GEMM on the
  * pieces (fractional selectors stay in fp32 in both; GEMM tiles that hold one
  * take about twice as long).
+ * Beyond 16 tokens a pruned group adds nothing, whatever X holds; up to 16, a
+ * non-finite X of a pruned group may make Y NaN, as in place.
  *   X [T, d_in] bf16; Wp, chunk, scale, rowptr as written by gm_pack_rows,
  *   which must have held every kept group (rowptr[d_out] <= its capacity);
  *   g is the width of the exported pieces (the group width; a square export

@@ -119,7 +119,7 @@ __global__ __launch_bounds__(64 * kFwdWaves) void fwd_kernel(const uint16_t* __r
   __shared__ uint32_t s_any[MAXU / 32];       // unit kept by some row of the tile
   __shared__ int s_cols[MAXU];
   __shared__ uint32_t s_live[GO >= 32 ? MAXU : 1];  // per listed unit: bit f = 16-row fragment f of the tile keeps it
-  __shared__ int s_ncols, s_soft;
+  __shared__ int s_ncols, s_soft, s_nan;
 
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -136,6 +136,7 @@ __global__ __launch_bounds__(64 * kFwdWaves) void fwd_kernel(const uint16_t* __r
   if (tid < MAXU / 32) s_any[tid] = 0;
   if (tid == 0) {
     s_soft = 0;
+    if constexpr (PACKED) s_nan = 0;
     s_cols[0] = 0;  // read (unused) by the zero-fill copies when no unit is kept
   }
   const int words = (G_in + 31) / 32;
@@ -447,6 +448,7 @@ __global__ __launch_bounds__(64 * kFwdWaves) void fwd_kernel(const uint16_t* __r
                                      __builtin_bit_cast(bf16x8_t, ah), __builtin_bit_cast(bf16x8_t, bf[nb]),
                                      f32x4{0.0f, 0.0f, 0.0f, 0.0f}, 0, 0, 0);
           }
+          if constexpr (MB > 4) __builtin_amdgcn_sched_barrier(0);
         }
       }
       wait_vmcnt<0>();  // zero-fill copies of slices past the end
@@ -460,6 +462,9 @@ __global__ __launch_bounds__(64 * kFwdWaves) void fwd_kernel(const uint16_t* __r
         Ag, Bg, nst, wm * MB * 16, wn * NB * 16, lane, acc, prepare, issue, [](int) {},
         [](int, const u32x4(&)[NB]) {}, live);
 
+  // Packed: a pruned group's zeros times a non-finite X make its row NaN; such a tile's rows are computed again below.
+  if constexpr (PACKED)
+    if (any_nan(acc)) s_nan = 1;
   if constexpr (KS == 1) {
     if (part) {
 #pragma unroll
@@ -489,6 +494,20 @@ __global__ __launch_bounds__(64 * kFwdWaves) void fwd_kernel(const uint16_t* __r
                                              reinterpret_cast<char*>(smem) + NW * HC * NB * 1024, kg, wg, wm, wn, tid,
                                              lane, Y, d_out, n0, T, m0, d_out);
   }
+  if constexpr (PACKED)
+    if (s_nan) {  // (visible: the stores above have barriers)
+      // The arguments are read again: kept through the K-loop they cost the largest tiles registers.
+      const auto* args = (const volatile __attribute__((address_space(4))) uint64_t*)(__builtin_amdgcn_kernarg_segment_ptr());
+      const uint16_t* Xa = reinterpret_cast<const uint16_t*>(args[0]);
+      const uint16_t* Wa = reinterpret_cast<const uint16_t*>(args[1]);
+      uint16_t* Ya = reinterpret_cast<uint16_t*>(args[5]);
+      const int* ca = reinterpret_cast<const int*>(args[8]);
+      const int* ra = reinterpret_cast<const int*>(args[9]);
+      const float* sa = reinterpret_cast<const float*>(args[10]);
+      __threadfence();  // the tile's stores
+      __syncthreads();
+      packed_rows(Xa, Wa, ca, sa, ra, m0 + wave, min(m0 + BM, d_out), NW, n0, min(n0 + BN, T), d_in, d_out, G, lane, Ya);
+    }
 }
 
 // Y = bf16(sum over shares s = 0 .. ksplit-1 of part[s]), eight outputs per thread.

@@ -14,7 +14,7 @@ constexpr int kWtMaskRows = 2048;
 struct WtMask {
   uint16_t bits[kWtMaskRows];
   uint16_t list[kWtMaskRows];
-  int nlist;
+  int nlist, nan;
 };
 
 constexpr int wt_stages(int BM, int BN, int KS) { return KS * (BM + BN) > 512 ? 3 : 4; }
@@ -60,7 +60,7 @@ __device__ __forceinline__ bool wt_mask(const float* __restrict__ mask, int G_ou
       if (f) sm.list[cnt + __popcll(bal & ((uint64_t(1) << lane) - 1))] = uint16_t(u);
       cnt += __popcll(bal);
     }
-    if (lane == 0) sm.nlist = cnt;
+    if (lane == 0) sm.nlist = cnt, sm.nan = 0;
   }
   __syncthreads();
   return soft;
@@ -109,7 +109,7 @@ __device__ __forceinline__ void wt_kept_only(const uint16_t* __restrict__ B, int
 template <int G, int BM, int BN, int KS, bool WALK>
 __device__ __forceinline__ void wt_tile(const uint16_t* __restrict__ B, int ldb, const uint16_t* __restrict__ W, int K,
                                         int d, int N, const float* __restrict__ mask, uint16_t* __restrict__ out,
-                                        u32x4* smem, const WtMask* sm, float* s_msoft, int m0, int n0, bool soft) {
+                                        u32x4* smem, WtMask* sm, float* s_msoft, int m0, int n0, bool soft) {
   constexpr int NW = 8, NG = NW / KS, WN = NG / 2;
   constexpr int MB = BM / 32, NB = BN / WN / 16;
   constexpr int CA = BM / 16 / NG, CB = BN / 16 / NG, PER_STAGE = CA + CB;
@@ -259,8 +259,8 @@ __device__ __forceinline__ void wt_tile(const uint16_t* __restrict__ B, int ldb,
   }
   int et = tid, el = lane;  // opaque: the epilogue's addresses are not computed (and kept in registers) before the K-loop
   asm volatile("" : "+v"(et), "+v"(el));
-  bool nan = false;
-  if constexpr (G > 0) nan = __syncthreads_or(any_nan(acc));
+  if constexpr (G > 0)
+    if (any_nan(acc)) sm->nan = 1;
   if constexpr (KS == 1)
     store_tile_rows<BM, MB, NB, NW>(acc, reinterpret_cast<char*>(smem), reinterpret_cast<char*>(smem + STAGES * BM * 4),
                                     wm, wn, et, el, out, d, n0, N, m0, d);
@@ -269,7 +269,8 @@ __device__ __forceinline__ void wt_tile(const uint16_t* __restrict__ B, int ldb,
                                              reinterpret_cast<char*>(smem) + NW * HC * NB * 1024, kg, wg, wm, wn, et,
                                              el, out, d, n0, N, m0, d);
   if constexpr (G > 0)
-    if (nan) wt_kept_only<G, BM, BN>(B, ldb, W, K, d, N, mask, out, sm->bits, m0, n0);
+    if (sm->nan)  // (visible: the stores above have barriers)
+      wt_kept_only<G, BM, BN>(B, ldb, W, K, d, N, mask, out, sm->bits, m0, n0);
 }
 
 // Every row of W'.

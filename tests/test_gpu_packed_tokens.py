@@ -149,3 +149,39 @@ def test_one_token_more_than_16_costs_little():
     b = _best(lambda: gm.gm_packed_linear_fwd(X, *packed, d_out, g, Y))
     say(f"packed {d_out} x {d_in}: 16 tokens {100 * a:.1f} us, 17 tokens {100 * b:.1f} us")
     assert b < 3.0 * a
+
+
+@pytest.mark.parametrize("soft", [False, True])
+@pytest.mark.parametrize("T,d_in,d_out,g", [
+    (17, 1024, 264, 128),     # passes
+    (300, 1024, 272, 16),     # 128 x 128 tiles
+    (300, 2048, 520, 256),
+    (2040, 512, 4088, 256),   # 256 x 128 tiles
+    (4090, 512, 4088, 128),   # 256 x 256 tiles
+])
+def test_packed_pruned_groups_ignore_non_finite_x(T, d_in, d_out, g, soft):
+    # an infinite or NaN X[t, i] reaches Y[t, o] only through a kept group of (o, i)
+    import paper_2609_33977_amd as gm
+    say(f"packed, non-finite X: T={T} d_in={d_in} d_out={d_out} g={g} soft={soft}")
+    g_out = g if g < 64 else 1
+    case = workloads.make_linear_case((313, T, d_in, d_out, g), T, d_in, d_out, g, None, g_out=g_out)
+    r = workloads.gen.rng_for(314, T, g)
+    mask = (r.uniform(size=case.mask.shape) < 0.4).astype(np.float32)
+    if soft:
+        mask *= r.uniform(0.05, 1.5, size=mask.shape).astype(np.float32)
+    bad = {(0, 3): 0x7F80, (T - 1, d_in - 1): 0xFF80, (T // 2, d_in // 2): 0x7FC0}
+    X, clean, hit = case.X.copy(), case.X.copy(), np.zeros((T, d_out), dtype=bool)
+    for (t, i), bits in bad.items():
+        X[t, i], clean[t, i] = bits, 0
+        hit[t] |= np.repeat(mask[:, i // g] != 0, g_out)
+    packed = _pack(dev_bf16(case.W), dev_f32(mask), g, g_out)
+    Y = empty_bf16(T, d_out)
+    gm.gm_packed_linear_fwd(dev_bf16(X), *packed, d_out, g, Y)
+    sync()
+    got = host_f64_from_bf16(Y)
+    assert not np.any(np.isfinite(got[hit])), "a kept group's infinity or NaN is lost"
+    Xo, Wo = oracle.from_bf16(clean), oracle.from_bf16(case.W)
+    ref = oracle.linear_fwd(Xo, Wo, mask, g, g_out)
+    b = _bound(Xo, Wo, mask, g, g_out, ref)
+    got[hit], ref[hit] = 0.0, 0.0
+    assert_close("Y", got, ref, bound=b)
