@@ -46,6 +46,9 @@ def _soften(mask, key):
     (257, 576, 96, 32, 32),
     (1100, 4096, 160, 32, 32),  # 256 x 128 tiles
     (4000, 4096, 64, 16, 16),   # 256 x 256 tiles
+    (17, 64, 32784, 16, 16),    # more mask rows than such a tile holds: 64 x 256 tiles over lists of four
+    (17, 64, 65568, 32, 32),    # ... and of two groups
+    (300, 128, 65568, 32, 32),
 ])
 def test_dx_tiles(T, d_in, d_out, g, g_out, soft):
     say(f"dX tiles: T={T} d_in={d_in} d_out={d_out} g={g} g_out={g_out} soft={soft}")
