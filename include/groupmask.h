@@ -158,6 +158,8 @@ gm_status gm_gate_bwd_budget(const float* dgate, const float* soft, int64_t n, f
  * needs one only for launches of few output tiles (at most 128 tiles of
  * 256 x 256, e.g. T = 512 with d_out = 5120), where it may split K: then
  * ksplit * T * d_out fp32 for the partial tiles (ksplit <= 8); otherwise 0.
+ * The backward's size depends on the shape alone: 16 x 16 and 32 x 32 groups of
+ * at most 2048 mask rows need the same as others, though their dX reads none of it.
  *   bytes: HOST pointer, required.
  */
 gm_status gm_workspace_size(int op, int64_t T, int64_t d_in, int64_t d_out, int32_t g, int32_t g_out,

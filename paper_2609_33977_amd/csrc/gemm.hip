@@ -809,6 +809,7 @@ __global__ __launch_bounds__(64 * dx_waves(BM, KS)) void dx_kernel(const uint16_
   constexpr int HC = BM == 256 ? MB / 4 : MB / 2;
   static_assert(KS == 1 || KS * STAGES * (BM + BN) * 64 >= NW * HC * NB * 1024 + 2 * BM * BN, "LDS");
   static_assert(KR * NSUB <= 64, "one lane per selector of a wave's rows");
+  static_assert(KS == 1 || NSUB == 1, "one K group for list columns of several groups");
   __shared__ u32x4 smem[KS * STAGES * (BM + BN) * 4];  // the W rings, then the dY^T rings; afterwards the output tile
   // (the 64 x 256 tile's ring is half a CU's LDS: its soft selectors come from memory)
   constexpr bool MS = BM > 64 || KS > 1;
@@ -914,14 +915,7 @@ __global__ __launch_bounds__(64 * dx_waves(BM, KS)) void dx_kernel(const uint16_
       rowB[q] = k0 + q < kv ? uint32_t(idx[q]) * uint32_t(ldt) * 2u : kOOB;
     }
 #pragma unroll
-    for (int j = 0; j < NA; ++j) {
-      offA[j] = pick(rowA, j, RPI_A, lane / (BM / 8)) + colA[j];
-      if constexpr (NSUB > 1) {
-        int row, c;
-        mn_dma_target<BM>((wg * NA + j) * 64 + lane, row, c);
-        offA[j] |= ((~pick(kbits, j, RPI_A, lane / (BM / 8)) >> (c / CPS)) & 1u) << 31;
-      }
-    }
+    for (int j = 0; j < NA; ++j) offA[j] = pick(rowA, j, RPI_A, lane / (BM / 8)) + colA[j];
 #pragma unroll
     for (int j = 0; j < NBC; ++j) offB[j] = (pick(rowB, j, RPI_B, lane / (BN / 8)) + colB[j]) | pastB[j];
     load_idx(st + 1);
