@@ -126,52 +126,6 @@ size_t fwd_workspace(int64_t T, int64_t d_in, int64_t d_out, int32_t g) {
   return ks > 1 ? round_up(size_t(ks) * size_t(T) * size_t(d_out) * sizeof(float), 256) : 0;
 }
 
-// Tile of the forward GEMM: the one with the lowest estimated time, rounds of
-// blocks (gm::rounds_ns) that take a fixed time (launch, mask bits, pipeline
-// fill, epilogue) and a time per 32-deep K slice.  Measured (4096 x 4096, half the groups kept): 256 x 256 tiles 15 us + 0.66
-// us per slice; 256 x 128 (K over two wave groups) 14 us + 0.42; 128 x 128
-// (same) 9 us + 0.25; a K split over blocks adds a reduction of 4 us and 8
-// bytes per output and share (mostly cached: 15 TB/s for the few shares of 256 x
-// 256 tiles, 8 TB/s for up to eight of 128 x 128 ones).  Splitting the smaller
-// tile: 4096 x 4096, T = 128 22 us (unsplit 38, 256 x 256 split in eight 28), T =
-// 512 31 (39, 40); 4096 x 11008 inputs, T = 128 28 (92, 44); 2816 x 2056, T = 300
-// 19 (28, 29).  The model picks the
-// fastest or within 3 % of it at T = 128 .. 4096 on 1024^2, 2816 x 2056, 4096^2,
-// 11008 x 4096 (both ways) and the LLaMA-2-13B shapes: e.g. T = 2048 at 4096^2
-// 65 us in 256 x 128 tiles (256 x 256 split in two: 73), T = 1024 41 us in 128 x
-// 128 tiles (split in four: 50), T = 4096 98 us in 256 x 256 tiles (125).
-struct FwdPlan {
-  gm::FwdTile tile;
-  int ks;
-  int64_t ns;  // estimated time
-};
-
-bool fwd_tile_fits(gm::FwdTile tile, int64_t d_in, int32_t g, int32_t g_out, bool packed) {
-  if (tile == gm::FwdTile::k128x128) return true;
-  if (g < 32 || (packed && g < 64)) return tile == gm::FwdTile::k256x256 && !packed;
-  if (g_out != 1 || (tile == gm::FwdTile::k256x256 && !packed)) return true;
-  return d_in / g <= gm::fwd_max_groups(g, packed, tile == gm::FwdTile::k256x128);
-}
-
-// ks: shares of the 256 x 256 tile's K range (1 without a workspace).
-FwdPlan fwd_plan(int64_t T, int64_t d_in, int64_t d_out, int32_t g, int32_t g_out, bool packed, int ks) {
-  using gm::FwdTile;
-  const int64_t slices = d_in / 32;
-  auto tiles = [&](int64_t bm, int64_t bn) { return ((d_out + bm - 1) / bm) * ((T + bn - 1) / bn); };
-  auto reduce_ns = [&](int64_t k, int64_t rate) { return 4000 + k * T * d_out * 8 / rate; };  // rate: bytes per ns
-  FwdPlan best{FwdTile::k128x128, 1, gm::rounds_ns(tiles(128, 128), 9000 + 250 * slices)};
-  auto consider = [&](FwdTile tile, int k, int64_t ns) {
-    if (ns < best.ns) best = {tile, k, ns};
-  };
-  for (int k = 2; k <= ks; ++k)  // ks: what the workspace holds
-    consider(FwdTile::k128x128, k, gm::rounds_ns(tiles(128, 128) * k, 9000 + 250 * slices / k) + reduce_ns(k, 8000));
-  if (fwd_tile_fits(FwdTile::k256x128, d_in, g, g_out, packed))
-    consider(FwdTile::k256x128, 1, gm::rounds_ns(tiles(256, 128), 14000 + 420 * slices));
-  if (fwd_tile_fits(FwdTile::k256x256, d_in, g, g_out, packed))
-    consider(FwdTile::k256x256, ks, gm::rounds_ns(tiles(256, 256) * ks, 15000 + 660 * slices / ks) + (ks > 1 ? reduce_ns(ks, 15000) : 0));
-  return best;
-}
-
 // Workspace of the backward, each part 256-byte aligned, over NL = d_in / lc
 // list columns of lc = max(g, 64) input columns (nsub = lc / g groups each):
 //   colcount [NL] int32 | colsoft [NL] int32 | rows [NL * d_out + 128] int32 |
@@ -411,7 +365,7 @@ GM_EXPORT gm_status gm_masked_linear_fwd(const uint16_t* X, const uint16_t* W, c
   if (T <= kDecodeTokens && d_in / g <= gm::gemv_max_groups_per_row())
     return from_hip(gm::launch_gemv_inplace(X, W, mask, t, di, dout, g, g_out, Y, stream));
   // Without a workspace no tile's K range is split over blocks (the same Y up to fp32 summation order).
-  const FwdPlan p = fwd_plan(T, d_in, d_out, g, g_out, false, ws && need ? fwd_splits(T, d_in, d_out, g) : 1);
+  const gm::FwdPlan p = gm::fwd_plan(T, d_in, d_out, g, g_out, false, ws && need ? fwd_splits(T, d_in, d_out, g) : 1);
   return from_hip(gm::launch_fwd(X, W, mask, t, di, dout, g, g_out, Y, p.tile, p.ks, static_cast<float*>(ws), stream));
 }
 
@@ -553,7 +507,7 @@ GM_EXPORT gm_status gm_packed_linear_fwd(const uint16_t* X, const uint16_t* Wp, 
     return GM_ERR_ALIGN;
   if (gm_status st = check_device()) return st;
   if (T > kDecodeTokens) {
-    const FwdPlan p = fwd_plan(T, d_in, d_out, g, 1, true, 1);
+    const gm::FwdPlan p = gm::fwd_plan(T, d_in, d_out, g, 1, true, 1);
     if (!gm::packed_passes(T, d_in, d_out, g, p.ns))
       return from_hip(gm::launch_fwd_packed(X, Wp, chunk, scale, rowptr, int(T), int(d_in), int(d_out), g, Y, p.tile,
                                             stream));

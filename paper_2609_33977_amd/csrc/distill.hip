@@ -404,20 +404,14 @@ hipError_t launch_distill_bwd(const uint16_t* W, int N, int d, int V, const floa
                      wtok, N, V, ldv, dz);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  // The tile with the fewest estimated rounds of 256 blocks times the time per
-  // K slice (cold head and dz: 0.72 us for 256 x 256, 0.60 for 256 x 128, 0.37
-  // for 128 x 128, measured at V = 32000, d = 4096): N = 4096 keeps 256 x 256
-  // (0.93 ms against 1.18 and 1.56), N = 2048 takes 256 x 128 (0.60 ms against
-  // 0.72 and 0.73), N <= 1024 128 x 128 (0.37 ms against 0.70 and 0.51).
-  auto blocks = [&](int bm, int bn) { return int64_t((d + bm - 1) / bm) * ((N + bn - 1) / bn); };
-  const int64_t big = rounds_ns(blocks(256, 256), 720), half = rounds_ns(blocks(256, 128), 600),
-                mid = rounds_ns(blocks(128, 128), 370);
+  auto blocks = [&](int bm, int bn) { return tile_blocks(d, N, bm, bn); };
+  const WtTile tile = lm_bwd_tile(N, d);
 #define GM_LM_BWD(BM, BN, KS)                                                                                \
   hipLaunchKernelGGL((lmhead_bwd_kernel<BM, BN, KS>), dim3(unsigned(blocks(BM, BN))), dim3(64 * kLmWaves), 0, s, dz, \
                      ldv, W, N, d, V, dH)
-  if (mid < half && mid < big)
+  if (tile == WtTile::k128x128)
     GM_LM_BWD(128, 128, 2);
-  else if (half < big)
+  else if (tile == WtTile::k256x128)
     GM_LM_BWD(256, 128, 2);
   else
     GM_LM_BWD(256, 256, 1);

@@ -1126,17 +1126,8 @@ hipError_t launch_dgate(const uint16_t* dY, const uint16_t* X, const uint16_t* W
     if (e != hipSuccess) return e;
   }
   auto tiles = [&](int bn) { return ((d_in + 255) / 256) * ((d_out + bn - 1) / bn); };
-  // The tile with the lowest estimated time: rounds of 256 blocks (a partly
-  // empty last round costs a whole one) of 13 us + 0.62 us per K slice for 256 x
-  // 256, 13 + 0.415 for 256 x 128, 7 + 0.32 for 256 x 64 (1 x g groups only: its
-  // waves hold 32 columns).  E.g. 1024 x 1024, T = 2048: 49 us in 256 x 256, 40 in
-  // 256 x 128, 26 in 256 x 64; 2816 x 2056, T = 1000: 34 / 27 / 33; 4096 x 4096, T
-  // = 2048: 61 / 80 / 104.
-  const int64_t sl = (T + 31) / 32;
-  auto est = [&](int bn, int64_t ns) { return int64_t((tiles(bn) + 255) / 256) * ns; };
-  const int64_t big = est(256, 13000 + 620 * sl), half = est(128, 13000 + 415 * sl),
-                low = go == 1 ? est(64, 7000 + 320 * sl) : INT64_MAX;
-  if (low < half && low < big) {
+  const int columns = dgate_columns(T, d_in, d_out, go);
+  if (columns == 64) {
     switch (g) {
       GM_CASE_G1(dgate_low, 64, tiles(64) + la.nunits, 64 * kDgateWaves, dY, X, W, T, d_in, d_out, dgate, dYt, ldt, la)
       GM_CASE_G1(dgate_low, 128, tiles(64) + la.nunits, 64 * kDgateWaves, dY, X, W, T, d_in, d_out, dgate, dYt, ldt, la)
@@ -1144,7 +1135,7 @@ hipError_t launch_dgate(const uint16_t* dY, const uint16_t* X, const uint16_t* W
       GM_CASE_G1(dgate_low, 512, tiles(64) + la.nunits, 64 * kDgateWaves, dY, X, W, T, d_in, d_out, dgate, dYt, ldt, la)
       default: return hipErrorInvalidValue;
     }
-  } else if (half < big) {
+  } else if (columns == 128) {
     GM_LAUNCH_G(dgate_half, tiles(128) + la.nunits, 64 * kDgateWaves, dY, X, W, T, d_in, d_out, dgate, dYt, ldt, la)
   } else {
     GM_LAUNCH_G(dgate_kernel, tiles(256) + la.nunits, 64 * kDgateWaves, dY, X, W, T, d_in, d_out, dgate, dYt, ldt, la)
@@ -1174,60 +1165,29 @@ hipError_t launch_dx(const uint16_t* dYt, int ldt, const uint16_t* W, const int*
     GM_DX(64, 256, 1, 2);
     return hipGetLastError();
   }
-  // The tile with the lowest estimated time among those that divide the list
-  // column; the slices of a column are taken as half its rows.  Us per block
-  // and round + us per 32-deep slice, fitted to LLaMA-2-7B shapes at T = 128 ..
-  // 4096, half the groups kept: 256 x 256 19 + 0.64, 256 x 128 (two K groups)
-  // 16 + 0.49, 128 x 256 14 + 0.62, 128 x 128 (two) 13 + 0.39, 64 x 128 (two)
-  // 15 + 0.29; the 64 x 256 tile runs two blocks per CU (13 + 0.78 per round of
-  // 512, 13 + 0.50 below half of one).  E.g. 4096 x 4096, 1 x 256 groups: T =
-  // 4096 67 us in 256 x 256 tiles (96 in 256 x 128), T = 2048 51 in 256 x 128 (59),
-  // T = 1024 38 in 128 x 128 (58), T = 128 32 in 64 x 128 (44 in 64 x 256); 11008
-  // rows, T = 1024 81 in 128 x 128 (128 in 256 x 256).
-  const int64_t sl = (d_out + 63) / 64;
-  enum { kBig, kHalf, kWide, kMid, kLow, kPair } tile = kLow;
-  int64_t best = rounds_ns(blocks(64, 128), 15000 + 290 * sl);
-  auto consider = [&](auto t, int64_t ns) {
-    if (ns < best) tile = t, best = ns;
-  };
-  if (lc >= 128) consider(kMid, rounds_ns(blocks(128, 128), 13000 + 390 * sl));
-  if (lc == 128) consider(kWide, rounds_ns(blocks(128, 256), 14000 + 620 * sl));
-  if (lc >= 256) consider(kHalf, rounds_ns(blocks(256, 128), 16000 + 490 * sl));
-  if (lc >= 256) consider(kBig, rounds_ns(blocks(256, 256), 19000 + 640 * sl));
-  if (lc == 64)
-    consider(kPair, blocks(64, 256) <= 256 ? 13000 + 500 * sl : rounds_ns(blocks(64, 256) / 2, 13000 + 780 * sl));
-  switch (tile) {
-    case kBig: GM_DX(256, 256, 1, 1); break;
-    case kHalf: GM_DX(256, 128, 2, 1); break;
-    case kWide: GM_DX(128, 256, 1, 1); break;
-    case kMid: GM_DX(128, 128, 2, 1); break;
-    case kLow: GM_DX(64, 128, 2, 1); break;
-    case kPair: GM_DX(64, 256, 1, 1); break;
+  switch (dx_tile(T, d_in, d_out, g)) {
+    case DxTile::kBig: GM_DX(256, 256, 1, 1); break;
+    case DxTile::kHalf: GM_DX(256, 128, 2, 1); break;
+    case DxTile::kWide: GM_DX(128, 256, 1, 1); break;
+    case DxTile::kMid: GM_DX(128, 128, 2, 1); break;
+    case DxTile::kLow: GM_DX(64, 128, 2, 1); break;
+    case DxTile::kPair: GM_DX(64, 256, 1, 1); break;
   }
 #undef GM_DX
   return hipGetLastError();
 }
 
-bool dx_dense_ok(int d_out, int g) { return g < 64 && d_out / g <= kWtMaskRows; }
-
 hipError_t launch_dx_dense(const uint16_t* dY, const uint16_t* W, const float* mask, int T, int d_in, int d_out, int g,
                            uint16_t* dX, hipStream_t s) {
   auto blocks = [&](int bm, int bn) { return int64_t((d_in + bm - 1) / bm) * ((T + bn - 1) / bn); };
-  // The tile with the lowest estimated time (us per block and round: 10 + 0.70
-  // per K slice for 256 x 256, 11 + 0.45 for 256 x 128, 7 + 0.24 for 128 x 128;
-  // 4096 x 4096, 32 x 32 groups: T = 4096 101 / 127 / 150 us, T = 2048 97 / 69 /
-  // 78, T = 512 88 / 60 / 37).
-  const int64_t slices = (d_out + 31) / 32;
-  const int64_t big = rounds_ns(blocks(256, 256), 10000 + 700 * slices),
-                half = rounds_ns(blocks(256, 128), 11000 + 450 * slices),
-                mid = rounds_ns(blocks(128, 128), 7000 + 240 * slices);
 #define GM_DENSE(G, BM, BN, KS)                                                                                  \
   hipLaunchKernelGGL((dx_dense_kernel<G, BM, BN, KS>), dim3(unsigned(blocks(BM, BN))), dim3(512), 0, s, dY, W, mask, T, \
                      d_in, d_out, dX)
+  const WtTile tile = dx_dense_tile(T, d_in, d_out);
 #define GM_DENSE_G(G)                        \
-  if (mid < half && mid < big)               \
+  if (tile == WtTile::k128x128)              \
     GM_DENSE(G, 128, 128, 2);                \
-  else if (half < big)                       \
+  else if (tile == WtTile::k256x128)         \
     GM_DENSE(G, 256, 128, 2);                \
   else                                       \
     GM_DENSE(G, 256, 256, 1);

@@ -3,11 +3,9 @@
 #pragma once
 
 #include "gm_gemm.h"
+#include "gm_plan.h"
 
 namespace gm {
-
-// Mask rows a block holds the kept bits of (small square groups).
-constexpr int kWtMaskRows = 2048;
 
 // Selectors of a tile's columns (small square groups): per mask row the kept
 // bits of the tile's 16-column fragments, and the rows that keep any.

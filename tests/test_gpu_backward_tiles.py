@@ -31,27 +31,38 @@ def _soften(mask, key):
     return soft
 
 
+# Each list gives the tile that the library chooses for the shape (checked on the CPU by test_tile_plan.py).
+DX_TILES = [
+    (17, 64, 8, 64, 1, "64x256"),
+    (40, 1024, 2056, 512, 1, "64x128"),     # ragged tokens and rows
+    (128, 4096, 1056, 256, 1, "128x128"),
+    (128, 4096, 4104, 256, 1, "64x128"),
+    (130, 1024, 1032, 256, 1, "128x128"),
+    (260, 512, 512, 512, 1, "128x128"),
+    (1030, 2816, 520, 128, 1, "128x128"),
+    (2041, 4096, 264, 256, 1, "256x128"),
+    (4090, 4096, 264, 512, 1, "256x256"),
+    (2050, 4096, 264, 128, 1, "128x256"),
+    (300, 384, 384, 128, 128, "128x128"),
+    (1000, 16384, 128, 64, 64, "64x256"),   # two blocks per CU
+    (33, 64, 32, 16, 16, "dense 128x128"),  # every row: one slice, a single mask-row pair
+    (140, 320, 336, 16, 16, "dense 128x128"),  # K not a multiple of 32, columns past the last tile
+    (257, 576, 96, 32, 32, "dense 128x128"),
+    (1100, 4096, 160, 32, 32, "dense 128x128"),
+    (2041, 4096, 160, 32, 32, "dense 256x128"),
+    (2041, 4096, 144, 16, 16, "dense 256x128"),
+    (4090, 4096, 96, 32, 32, "dense 256x256"),
+    (4000, 4096, 64, 16, 16, "dense 256x256"),
+    (17, 64, 32784, 16, 16, "64x256"),      # more mask rows than a tile holds: lists of four groups a column
+    (17, 64, 65568, 32, 32, "64x256"),      # ... and of two
+    (300, 128, 65568, 32, 32, "64x256"),
+]
+
+
 @pytest.mark.parametrize("soft", [False, True])
-@pytest.mark.parametrize("T,d_in,d_out,g,g_out", [
-    (17, 64, 8, 64, 1),         # one slice: the second K group has none
-    (130, 1024, 1032, 256, 1),  # 64 x 128 tiles of 256-wide columns, ragged tokens and rows
-    (260, 512, 512, 512, 1),
-    (1030, 2816, 520, 128, 1),  # 128 x 128 tiles
-    (2050, 4096, 264, 256, 1),  # 256 x 128 tiles
-    (2050, 4096, 264, 128, 1),  # 128 x 256 tiles
-    (300, 384, 384, 128, 128),
-    (1000, 16384, 128, 64, 64),  # 64 x 256 tiles, two blocks per CU
-    (33, 64, 32, 16, 16),       # every row: one slice, a single mask-row pair
-    (140, 320, 336, 16, 16),    # K not a multiple of 32, columns past the last tile
-    (257, 576, 96, 32, 32),
-    (1100, 4096, 160, 32, 32),  # 256 x 128 tiles
-    (4000, 4096, 64, 16, 16),   # 256 x 256 tiles
-    (17, 64, 32784, 16, 16),    # more mask rows than such a tile holds: 64 x 256 tiles over lists of four
-    (17, 64, 65568, 32, 32),    # ... and of two groups
-    (300, 128, 65568, 32, 32),
-])
-def test_dx_tiles(T, d_in, d_out, g, g_out, soft):
-    say(f"dX tiles: T={T} d_in={d_in} d_out={d_out} g={g} g_out={g_out} soft={soft}")
+@pytest.mark.parametrize("T,d_in,d_out,g,g_out,tile", DX_TILES)
+def test_dx_tiles(T, d_in, d_out, g, g_out, tile, soft):
+    say(f"dX tiles {tile}: T={T} d_in={d_in} d_out={d_out} g={g} g_out={g_out} soft={soft}")
     case = workloads.make_linear_case((290, T, d_in, d_out, g), T, d_in, d_out, g, None, g_out=g_out)
     mask = case.mask.astype(np.float32).copy()
     mask[:, -1] = 0.0  # a pruned column
@@ -88,24 +99,28 @@ def test_dx_does_not_read_unwritten_list_entries(T, d_in, d_out, g, g_out, fill)
     assert_close("dX", host_f64_from_bf16(dX), ref, bound=b)
 
 
-@pytest.mark.parametrize("T,d_in,d_out,g,g_out", [
-    (1, 64, 8, 64, 1),          # 256 x 64 tiles, one slice: the second K group has none
-    (33, 192, 72, 64, 1),       # a row past the first tile, columns past 128
-    (100, 1024, 1000, 512, 1),  # two tiles add to a group
-    (70, 640, 264, 128, 1),
-    (1000, 2816, 2056, 128, 1),  # 256 x 128 tiles
-    (900, 4096, 1032, 256, 1),
-    (650, 4096, 1000, 64, 1),
-    (700, 4096, 2000, 512, 1),
-    (40, 320, 336, 16, 16),     # square groups in 256 x 128 tiles
-    (33, 320, 160, 32, 32),
-    (200, 832, 448, 64, 64),
-    (65, 384, 384, 128, 128),
-    (300, 4096, 4096, 128, 128),  # 256 x 256 tiles
-    (130, 4096, 3848, 64, 1),
-])
-def test_dgate_tiles(T, d_in, d_out, g, g_out):
-    say(f"dgate tiles: T={T} d_in={d_in} d_out={d_out} g={g} g_out={g_out}")
+DGATE_TILES = [
+    (1, 64, 8, 64, 1, "256x64"),           # one slice: the second K group has none
+    (33, 192, 72, 64, 1, "256x64"),        # a row past the first tile, columns past 128
+    (100, 1024, 1000, 512, 1, "256x64"),   # two tiles add to a group
+    (70, 640, 264, 128, 1, "256x64"),
+    (1000, 2816, 2056, 128, 1, "256x128"),
+    (900, 4096, 1032, 256, 1, "256x128"),
+    (650, 4096, 1000, 64, 1, "256x64"),
+    (700, 4096, 2000, 512, 1, "256x128"),
+    (650, 4096, 2000, 64, 1, "256x128"),
+    (40, 320, 336, 16, 16, "256x128"),
+    (33, 320, 160, 32, 32, "256x128"),
+    (200, 832, 448, 64, 64, "256x128"),
+    (65, 384, 384, 128, 128, "256x128"),
+    (300, 4096, 4096, 128, 128, "256x256"),
+    (130, 4096, 3848, 64, 1, "256x256"),
+]
+
+
+@pytest.mark.parametrize("T,d_in,d_out,g,g_out,tile", DGATE_TILES)
+def test_dgate_tiles(T, d_in, d_out, g, g_out, tile):
+    say(f"dgate tiles {tile}: T={T} d_in={d_in} d_out={d_out} g={g} g_out={g_out}")
     import paper_2609_33977_amd as gm
     case = workloads.make_linear_case((293, T, d_in, d_out, g), T, d_in, d_out, g, None, g_out=g_out)
     dgate, dX = empty_f32(*case.mask.shape), empty_bf16(T, d_in)
@@ -121,15 +136,19 @@ def test_dgate_tiles(T, d_in, d_out, g, g_out):
     assert np.array_equal(alone.cpu().numpy(), dgate.cpu().numpy()), "dgate differs without dX beside it"
 
 
-@pytest.mark.parametrize("N,d,V", [
-    (1, 32, 8),
-    (130, 288, 1000),     # 128 x 128 tiles, ragged tokens, columns and vocabulary
-    (2050, 4096, 104),    # 256 x 128 tiles
-    (4100, 4096, 72),     # 256 x 256 tiles
-])
-def test_lmhead_backward_tiles(N, d, V):
+LM_TILES = [
+    (1, 32, 8, "128x128"),
+    (130, 288, 1000, "128x128"),  # ragged tokens, columns and vocabulary
+    (2041, 4096, 104, "256x128"),
+    (2050, 4096, 104, "256x256"),
+    (4100, 4096, 72, "256x256"),
+]
+
+
+@pytest.mark.parametrize("N,d,V,tile", LM_TILES)
+def test_lmhead_backward_tiles(N, d, V, tile):
     import paper_2609_33977_amd as gm
-    say(f"LM head backward tiles: N={N} d={d} V={V}")
+    say(f"LM head backward tiles {tile}: N={N} d={d} V={V}")
     case = workloads.make_distill_case((292, N, d, V), N, d, V)
     W = dev_bf16(case.W)
     ws = workspace(gm.gm_distill_workspace_size(N, d, V))

@@ -115,14 +115,17 @@ def test_a_fractional_export_costs_little_more_than_a_binary_one(T):
     assert s < 4.0 * h
 
 
-@pytest.mark.parametrize("T,d_in,d_out,g", [
+PASSES = [
     (17, 512, 8, 512),
     (32, 8256, 5120, 64),     # 129 groups per row: 16-row blocks
     (47, 4096, 5128, 128),    # 32-row blocks, 8 rows past the last
     (64, 1024, 1056, 32),
     (33, 16384, 64, 32),      # 512 groups per row
     (18, 5120, 4112, 16),     # 320 groups per row
-])
+]
+
+
+@pytest.mark.parametrize("T,d_in,d_out,g", PASSES)
 def test_packed_passes_of_16_tokens(T, d_in, d_out, g):
     import paper_2609_33977_amd as gm
     say(f"packed passes: T={T} d_in={d_in} d_out={d_out} g={g}")

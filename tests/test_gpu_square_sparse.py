@@ -25,19 +25,22 @@ def _sparse(case, kind, r):
     return m
 
 
+SHAPES = [
+    (140, 320, 336, 16, "dense 128x128"),
+    (257, 576, 1056, 32, "dense 128x128"),
+    (2041, 4096, 336, 16, "dense 256x128"),
+    (2041, 4096, 800, 32, "dense 256x128"),
+    (4090, 4096, 272, 16, "dense 256x256"),
+    (4090, 4096, 288, 32, "dense 256x256"),
+]
+
+
 @pytest.mark.parametrize("soft", [False, True])
 @pytest.mark.parametrize("kind", ["2 %", "10 %", "one row", "rows pruned", "columns pruned"])
-@pytest.mark.parametrize("T,d_in,d_out,g", [
-    (140, 320, 336, 16),     # 128 x 128 tiles
-    (257, 576, 1056, 32),
-    (2041, 4096, 336, 16),   # 256 x 128
-    (2041, 4096, 800, 32),
-    (4090, 4096, 272, 16),   # 256 x 256
-    (4090, 4096, 288, 32),
-])
-def test_dx_of_sparse_masks(T, d_in, d_out, g, kind, soft):
+@pytest.mark.parametrize("T,d_in,d_out,g,tile", SHAPES)
+def test_dx_of_sparse_masks(T, d_in, d_out, g, tile, kind, soft):
     import paper_2609_33977_amd as gm
-    say(f"sparse dX: T={T} d_in={d_in} d_out={d_out} g={g} {kind} soft={soft}")
+    say(f"sparse dX, {tile}: T={T} d_in={d_in} d_out={d_out} g={g} {kind} soft={soft}")
     case = workloads.make_linear_case((300, T, d_in, d_out, g), T, d_in, d_out, g, None, g_out=g)
     r = workloads.gen.rng_for(301, T, g)
     m = _sparse(case, kind, r)

@@ -37,19 +37,34 @@ def _both(case, mask):
     return Yi, Yp, packed
 
 
-@pytest.mark.parametrize("T,d_in,d_out,g,g_out", [
-    (17, 64, 8, 64, 1),            # one unit: the second wave group has a single slice
-    (129, 1536, 136, 512, 1),      # 128 x 128 tiles, one row and eight columns past the edge
-    (100, 8192, 144, 16, 16),      # 512 pieces of 16 weights per row
-    (130, 320, 160, 32, 32),
-    (2040, 512, 4088, 256, 1),     # 256 x 128 tiles, ragged both ways
-    (1100, 192, 8192, 64, 64),     # 256 x 128 tiles of square groups
-    (4090, 512, 4088, 128, 1),     # 256 x 256 tiles
-])
-def test_tiles_in_place_and_packed(T, d_in, d_out, g, g_out):
-    say(f"forward tiles: T={T} d_in={d_in} d_out={d_out} g={g} g_out={g_out}")
+# The tile that the library chooses for the shape in place and packed (checked on the CPU by test_tile_plan.py).
+FWD_TILES = [
+    (17, 64, 8, 64, 1, "128x128", "passes16"),           # one unit: the second wave group has a single slice
+    (129, 1536, 136, 512, 1, "128x128", "passes16"),     # one row and eight columns past the edge
+    (100, 8192, 144, 16, 16, "128x128", "passes16"),     # 512 pieces of 16 weights per row
+    (130, 320, 160, 32, 32, "128x128", "passes16"),
+    (700, 192, 1032, 64, 1, "128x128", "128x128"),
+    (900, 1536, 2056, 512, 1, "128x128", "128x128"),
+    (1000, 8192, 1040, 16, 16, "128x128", "128x128"),
+    (1000, 320, 2080, 32, 32, "128x128", "128x128"),
+    (2040, 512, 4088, 256, 1, "256x128", "256x128"),     # ragged both ways
+    (2041, 320, 4096, 32, 32, "256x128", "128x128"),
+    (2041, 192, 4096, 64, 64, "256x128", "256x128"),
+    (2041, 256, 4096, 128, 128, "256x128", "256x128"),
+    (1100, 192, 8192, 64, 64, "256x256", "256x256"),
+    (4090, 512, 4088, 128, 1, "256x256", "256x256"),
+    (4090, 320, 4096, 16, 16, "256x256", "128x128"),
+]
+
+
+@pytest.mark.parametrize("soft", [False, True])
+@pytest.mark.parametrize("T,d_in,d_out,g,g_out,tile,packed_tile", FWD_TILES)
+def test_tiles_in_place_and_packed(T, d_in, d_out, g, g_out, tile, packed_tile, soft):
+    say(f"forward tiles {tile}, packed {packed_tile}: T={T} d_in={d_in} d_out={d_out} g={g} g_out={g_out} soft={soft}")
     case = workloads.make_linear_case((280, T, d_in, d_out, g), T, d_in, d_out, g, None, g_out=g_out)
-    mask = case.mask.copy()
+    mask = case.mask.astype(np.float32).copy()
+    if soft:
+        mask *= workloads.gen.rng_for(284).uniform(0.05, 1.5, size=mask.shape).astype(np.float32)
     mask[-1] = 0.0  # a pruned row of groups
     Yi, Yp, _ = _both(case, mask)
     Xo, Wo = oracle.from_bf16(case.X), oracle.from_bf16(case.W)
