@@ -140,11 +140,17 @@ def _groups(d_out, d_in, g, g_out, where):
     return (d_out // g_out) * (d_in // g)
 
 
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+_raw_device = getattr(torch._C, "_cuda_getDevice", None)
+if _raw_device is None:
+    _raw_stream = None
+
+
 def _stream(stream):
-    # The current stream's handle without a Stream object around it (torch is
-    # initialised: the tensors' pointers were taken before).
+    # The current stream's handle without a Stream object around it where this
+    # torch has the call (torch is initialised: the tensors' pointers were taken before).
     if stream is None:
-        return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+        return _raw_stream(_raw_device()) if _raw_stream else torch.cuda.current_stream().cuda_stream
     return stream.cuda_stream
 
 

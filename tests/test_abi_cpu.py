@@ -348,3 +348,17 @@ def test_binding_rejects_wrong_dtypes_and_short_outputs_before_the_call():
         gm.gm_masked_linear_fwd(X, W, mask, g, Y)
     with pytest.raises(ValueError, match="must be contiguous"):
         gm.gm_gate_bwd(mask.t(), mask.t(), 0.5, mask.t())
+
+
+def test_binding_takes_the_current_stream_also_without_the_private_torch_call(monkeypatch):
+    import types
+
+    import torch
+    lib = gm._lib
+    monkeypatch.setattr(lib, "_raw_stream", lambda device: 100 + device)
+    monkeypatch.setattr(lib, "_raw_device", lambda: 3)
+    assert lib._stream(None) == 103
+    assert lib._stream(types.SimpleNamespace(cuda_stream=7)) == 7
+    monkeypatch.setattr(lib, "_raw_stream", None)
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda: types.SimpleNamespace(cuda_stream=9))
+    assert lib._stream(None) == 9
