@@ -17,7 +17,7 @@ OBJ = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libgroupmask.so")
 ARCH = "gfx950"
 
-SOURCES = ["gate.hip", "budget.hip", "index.hip", "gemv.hip", "gemm.hip", "distill.hip", "hyper.hip", "abi.cpp"]
+SOURCES = ["gate.hip", "budget.hip", "index.hip", "gemv.hip", "gemm.hip", "square.hip", "distill.hip", "hyper.hip", "abi.cpp"]
 
 # Packed fp32 VALU ops are kept out of the generated code; the host pass
 # warns that it does not know the feature, which is harmless.
@@ -37,7 +37,7 @@ COMMON = [
 # accumulators (sources that include gm_gemm.h) must stay at least 8 registers
 # below the 256 that two waves per SIMD allow (variants at 252-256 gave wrong
 # results).
-TIED_ACC_SOURCES = ("gemm.hip", "distill.hip")
+TIED_ACC_SOURCES = ("gemm.hip", "square.hip", "distill.hip")
 TIED_ACC_MAX_REGS = 248
 _REMARK = re.compile(r"remark:\s+(Function Name|VGPRs|AGPRs|ScratchSize \[bytes/lane\]|VGPRs Spill):\s*(\S+)")
 

@@ -381,13 +381,8 @@ gm_status masked_linear_bwd_launch(const uint16_t* dY, const uint16_t* X, const 
   const int t = int(T), di = int(d_in), dout = int(d_out), G_in = int(d_in / g);
   char* base = static_cast<char*>(ws);
   uint16_t* dyt = dX ? reinterpret_cast<uint16_t*>(base + L.dyt) : nullptr;
-  if (dX && gm::dx_dense_ok(dout, g)) {
-    if (dgate)
-      if (gm_status st = from_hip(gm::launch_dgate(dY, X, W, t, di, dout, g, g_out, dgate, nullptr, 0, nullptr, 1,
-                                                   nullptr, nullptr, nullptr, nullptr, nullptr, stream)))
-        return st;
-    return from_hip(gm::launch_dx_dense(dY, W, mask, t, di, dout, g, dX, stream));
-  }
+  if (dX && gm::dx_dense_ok(dout, g))
+    return from_hip(gm::launch_square_bwd(dY, X, W, mask, t, di, dout, g, dX, dgate, stream));
   if (dX) {
     int* colcount = reinterpret_cast<int*>(base + L.colcount);
     int* colsoft = reinterpret_cast<int*>(base + L.colsoft);

@@ -31,11 +31,11 @@
 //         first row of tiles stores for the dX GEMM.
 //   dX    K = the kept rows of one group column (its column list): whole rows
 //         of W and of dY^T are gathered, MN-major tiles, transposing reads.
+#include "gm_dgate.h"
 #include "gm_gemm.h"
 #include "gm_launch.h"
 #include "gm_lists.h"
 #include "gm_rows.h"
-#include "gm_wt.h"
 
 namespace gm {
 
@@ -43,15 +43,14 @@ namespace gm {
 // two per SIMD, so one wave's copy issue and barrier wait hide behind the
 // other's MFMAs.
 constexpr int kFwdWaves = 8;
-constexpr int kDgateWaves = 8;
 constexpr int kDxWaves = 8;
 // dX: 8 waves for tiles of 128 and 256 rows; the 64-row tile keeps 4 (its W
 // slice is four copies, one per wave).
 constexpr int dx_waves(int bm, int ks) { return bm >= 128 || ks > 1 ? kDxWaves : 4; }
 
 // MFMA rows of a wave tile issued after each slice's barrier (the K-loop's RA):
-// four for the forward and dgate (2.5-5 % faster than one), one for dX (level).
-constexpr int kFwdRowsAfter = 4, kDgateRowsAfter = 4, kDxRowsAfter = 1;
+// four for the forward (2.5-5 % faster than one), one for dX (level).
+constexpr int kFwdRowsAfter = 4, kDxRowsAfter = 1;
 
 // ============================================================================ fwd
 
@@ -530,239 +529,13 @@ __global__ __launch_bounds__(256) void fwd_reduce_kernel(const float* __restrict
 
 // ============================================================================ dgate
 
-// C[i, o] = sum_t X[t, i] dY[t, o], tile 256 (i) x BN (o); waves 2 (i) x WN (o).
-// The epilogue forms dgate[o, v] = sum_{i in v} W[o, i] C[i, o].  For g = 512 a
-// group spans two tiles, each adding its half onto a zeroed dgate (two
-// addends onto zero: the same sum whichever lands first).
-//
-// KS = 2: two wave groups split the tokens' slices (contiguous shares, the
-// last padded with zero slices) over their own rings, for launches with too
-// few 256 x 256 tiles to fill the chip.  The group sums are linear in C, so
-// each wave group weights and sums its own part of C, and only the group sums
-// are added, in LDS: no accumulators are exchanged (dgate of a 1024 x 1024
-// linear at T = 2048: 49 us in 16 256 x 256 tiles, 26 us in 64 256 x 64 tiles).
-//
-// Blocks past the tiles (when the dX GEMM follows) build the mask's column
-// lists, one col_lists_unit each: they start as the first tiles finish, on
-// CUs that would otherwise idle through the last tiles' tail (or a partial
-// last round of tiles), instead of in a launch of their own before dgate.
-struct ListArgs {
-  const float* mask;
-  int nunits, nchunks, nsub;
-  int *colcount, *colsoft, *rows, *subbits;
-  float* scales;
-};
-
-template <int G, int GO, int BN, int KS>
-__device__ __forceinline__ void dgate_tile(const uint16_t* __restrict__ dY, const uint16_t* __restrict__ X,
-                                           const uint16_t* __restrict__ W, int T, int d_in, int d_out,
-                                           float* __restrict__ dgate, uint16_t* __restrict__ dYt, int ldt,
-                                           const ListArgs& la) {
-  constexpr int NW = kDgateWaves, NG = NW / KS, WN = NG / 2;  // waves per block, per K group; wave grid 2 (i) x WN (o)
-  constexpr int BM = 256, MB = 8, NB = BN / WN / 16;
-  constexpr int CA = BM / 16 / NG, CB = BN / 16 / NG;  // copies of the X tile, of the dY tile per wave per slice
-  constexpr int PER_STAGE = CA + CB;
-  constexpr int STAGES = KS * (BM + BN) > 512 ? 3 : 4;
-  __shared__ u32x4 smem[KS * STAGES * (BM + BN) * 4];  // the X rings, then the dY rings; afterwards the group sums
-
-  const int tid = threadIdx.x, lane = tid & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int kg = wave / NG, wg = wave % NG;  // K group, wave within it
-  const int wm = wg / WN, wn = wg % WN;
-  const int G_in = d_in / G;
-  const int tiles_m = (d_in + BM - 1) / BM, tiles_n = (d_out + BN - 1) / BN, tiles = tiles_m * tiles_n;
-  if (int(blockIdx.x) >= tiles) {
-    col_lists_unit<64 * NW>(int(blockIdx.x) - tiles, la.nchunks, la.mask, d_out, G_in, GO, la.nsub, la.colcount,
-                            la.colsoft, la.rows, la.scales, la.subbits);
-    return;
-  }
-  u32x4(*As)[kBK * BM / 8] = reinterpret_cast<u32x4(*)[kBK * BM / 8]>(smem) + kg * STAGES;
-  u32x4(*Bs)[kBK * BN / 8] = reinterpret_cast<u32x4(*)[kBK * BN / 8]>(smem + KS * STAGES * BM * 4) + kg * STAGES;
-  int tm, tn;
-  tile_coords(int(blockIdx.x), tiles, tiles_m, tiles_n, tm, tn);
-  const int m0 = tm * BM, n0 = tn * BN;
-  const int all = (T + kBK - 1) / kBK, nst = (all + KS - 1) / KS;
-  const int s0 = kg * nst;  // this group's slices: [s0, s0 + nst), those from `all` on zeros
-
-  // Byte offsets of this lane's DMA chunks within a K slice (columns past the
-  // matrix read zeros; rows past T fall outside the slice's range).
-  uint32_t offA[CA], offB[CB];
-#pragma unroll
-  for (int j = 0; j < CA; ++j) {
-    int row, c;
-    mn_dma_target<BM>((wg * CA + j) * 64 + lane, row, c);
-    offA[j] = group_voffset(m0 + 8 * c < d_in ? uint32_t(row * d_in + m0 + 8 * c) * 2u : kOOB, j);
-  }
-#pragma unroll
-  for (int j = 0; j < CB; ++j) {
-    int row, c;
-    mn_dma_target<BN>((wg * CB + j) * 64 + lane, row, c);
-    offB[j] = group_voffset(n0 + 8 * c < d_out ? uint32_t(row * d_out + n0 + 8 * c) * 2u : kOOB, j);
-  }
-  const uint32_t bytesX = uint32_t(T) * uint32_t(d_in) * 2u;
-  const uint32_t bytesY = uint32_t(T) * uint32_t(d_out) * 2u;
-  i32x4_t rA, rB;  // buffer resources of the slice being copied (zero length past the end)
-  auto prepare = [&](int st) {
-    const bool live = st < nst && s0 + st < all;
-    const int k0 = live ? (s0 + st) * kBK : 0;
-    rA = make_rsrc_grouped(X + int64_t(k0) * d_in, live ? bytesX - uint32_t(k0) * uint32_t(d_in) * 2u : 0u);
-    rB = make_rsrc_grouped(dY + int64_t(k0) * d_out, live ? bytesY - uint32_t(k0) * uint32_t(d_out) * 2u : 0u);
-  };
-  const uint32_t ldsA = lds_addr(smem) + uint32_t(kg) * (STAGES * BM * 64);
-  const uint32_t ldsB = lds_addr(smem) + uint32_t(KS * STAGES * BM * 64) + uint32_t(kg) * (STAGES * BN * 64);
-  auto issue = [&](int st, int p) {  // copies 0 .. CA-1: X tile, CA .. CA+CB-1: dY tile
-    if (p < CA)
-      dma16_group(p, rA, offA[p], ldsA + (st % STAGES) * (kBK * BM * 2) + wg * CA * 1024);
-    else
-      dma16_group(p - CA, rB, offB[p - CA], ldsB + (st % STAGES) * (kBK * BN * 2) + wg * CB * 1024);
-  };
-
-  // dY^T side output (for the dX GEMM): lane (G, i) of a B fragment holds
-  // dY[k0 + 8 G .. k0 + 8 G + 7, o] for o = n0 + wn*NB*16 + nb*16 + i, which is a
-  // 16-byte chunk of row o of dY^T.  The tiles sharing this dY panel split
-  // the slices between them (slice kt goes to tile row kt * tiles_m / all), and
-  // within a tile the two wave rows, which hold the same B fragments, alternate.
-  // Buffer stores: one 32-bit offset per lane (out of range for rows past d_out).
-  const __amdgpu_buffer_rsrc_t rT =
-      __builtin_amdgcn_make_buffer_rsrc(dYt, short(0), int(uint32_t(d_out) * uint32_t(ldt) * 2u), 0x00020000);
-  const uint32_t offT = (uint32_t(n0 + wn * NB * 16 + (lane & 15)) * uint32_t(ldt) + 8u * uint32_t(lane >> 4)) * 2u;
-  auto bhook = [&](int st, const u32x4(&bf)[NB]) {
-    const int kt = s0 + st;
-    if (dYt == nullptr || (kt * tiles_m) / all != tm || (kt & 1) != wm) return;
-    if (kt * kBK + 8 * (lane >> 4) >= ldt) return;
-#pragma unroll
-    for (int nb = 0; nb < NB; ++nb)
-      __builtin_amdgcn_raw_buffer_store_b128(
-          bf[nb], rT,
-          n0 + wn * NB * 16 + nb * 16 + (lane & 15) < d_out ? offT + uint32_t(nb * 16 * ldt + kt * kBK) * 2u : kOOB, 0, 0);
-  };
-
-  f32x4 acc[MB][NB];
-  constexpr int RA = CA > 2 ? kDgateRowsAfter - 1 : kDgateRowsAfter;  // four copies' offsets take a row's registers
-  gemm_mainloop<MB, NB, false, false, BM, BN, PER_STAGE, STAGES, RA>(
-      As, Bs, nst, wm * 128, wn * NB * 16, lane, acc, prepare, issue, [](int) {}, bhook);
-
-  // Epilogue.  Lane (l >> 4, l & 15) holds, for every (mb, nb), rows
-  // i = i0 .. i0 + 3 of column o: W[o, i0 .. i0 + 3] is one 8-byte load.  The
-  // waves' sums meet in LDS once every wave has left its K-loop (its copies
-  // have drained), and are added in a fixed order.
-  int el = lane;  // opaque: the epilogue's addresses are not computed (and kept in registers) before the K-loop
-  asm volatile("" : "+v"(el));
-  const int ibase = m0 + wm * 128 + 4 * (el >> 4);
-  float* s_sum = reinterpret_cast<float*>(smem);
-  if constexpr (GO > 1) {
-    // Square groups (GO = G = 16 .. 128): a 16 x 16 fragment lies inside one
-    // group, so each lane sums its products per group of the wave's 128 (i) x
-    // 64 (o) sub-tile, and one reduction over the 64 lanes finishes the wave's
-    // share of each group.  Groups of 128 rows span two waves (wn pairs).
-    static_assert(NB == 4, "64 columns per wave");
-    constexpr int IB = 128 / G;                  // groups along i in a wave
-    constexpr int OS = GO < 64 ? 64 / GO : 1;    // groups (or group halves) along o in a wave
-    float part[IB][OS];
-#pragma unroll
-    for (int a = 0; a < IB; ++a)
-#pragma unroll
-      for (int b = 0; b < OS; ++b) part[a][b] = 0.0f;
-#pragma unroll
-    for (int nb = 0; nb < NB; ++nb) {
-      const int o = n0 + wn * NB * 16 + nb * 16 + (el & 15);
-#pragma unroll
-      for (int mb = 0; mb < MB; ++mb) {
-        const int i0 = ibase + mb * 16;
-        if (o < d_out && i0 < d_in) {
-          const uint2 w = *reinterpret_cast<const uint2*>(W + int64_t(o) * d_in + i0);
-          part[mb * 16 / G][nb * 16 / (GO < 64 ? GO : 64)] +=
-              acc[mb][nb][0] * bf16_lo(w.x) + acc[mb][nb][1] * bf16_hi(w.x) + acc[mb][nb][2] * bf16_lo(w.y) +
-              acc[mb][nb][3] * bf16_hi(w.y);
-        }
-      }
-    }
-    __syncthreads();
-#pragma unroll
-    for (int a = 0; a < IB; ++a)
-#pragma unroll
-      for (int b = 0; b < OS; ++b) {
-        float x = part[a][b];
-#pragma unroll
-        for (int d = 32; d >= 1; d >>= 1) x += __shfl_xor(x, d);
-        if (lane == 0) s_sum[(wave * IB + a) * OS + b] = x;
-      }
-    __syncthreads();
-    constexpr int NV = 256 / G, NU = BN / GO;  // groups of the tile along i, along o
-    const int b = tid % NU, a = tid / NU;      // at most 256 groups (16 x 16)
-    const int u = n0 / GO + b, v = m0 / G + a;
-    if (a < NV && u < d_out / GO && v < G_in) {
-      auto sum_of = [&](int k, int n) {  // the share of K group k's wave column n
-        return s_sum[(((k * 2 + a / IB) * WN + n) * IB + a % IB) * OS + (GO < 64 ? b % OS : 0)];
-      };
-      float x = 0.0f;
-#pragma unroll
-      for (int k = 0; k < KS; ++k) {
-        const float p = GO < 128 ? sum_of(k, b / OS) : sum_of(k, 2 * b) + sum_of(k, 2 * b + 1);
-        x = k == 0 ? p : x + p;
-      }
-      dgate[int64_t(u) * G_in + v] = x;
-    }
-  } else {
-    float part[NB][2];  // per o column: group sums over this wave's first / second 64 rows of i
-#pragma unroll
-    for (int nb = 0; nb < NB; ++nb) {
-      const int o = n0 + wn * NB * 16 + nb * 16 + (el & 15);
-      float s0 = 0.0f, s1 = 0.0f;
-#pragma unroll
-      for (int mb = 0; mb < MB; ++mb) {
-        const int i0 = ibase + mb * 16;
-        if (o < d_out && i0 < d_in) {
-          const uint2 w = *reinterpret_cast<const uint2*>(W + int64_t(o) * d_in + i0);
-          const float s = acc[mb][nb][0] * bf16_lo(w.x) + acc[mb][nb][1] * bf16_hi(w.x) +
-                          acc[mb][nb][2] * bf16_lo(w.y) + acc[mb][nb][3] * bf16_hi(w.y);
-          if (mb < MB / 2) s0 += s; else s1 += s;
-        }
-      }
-      // sum over the four lane groups (they hold the other i of the same o)
-      s0 += __shfl_xor(s0, 16);
-      s0 += __shfl_xor(s0, 32);
-      s1 += __shfl_xor(s1, 16);
-      s1 += __shfl_xor(s1, 32);
-      part[nb][0] = s0;
-      part[nb][1] = s1;
-    }
-    __syncthreads();
-    if (lane < 16) {
-#pragma unroll
-      for (int nb = 0; nb < NB; ++nb)
-#pragma unroll
-        for (int h = 0; h < 2; ++h) s_sum[((kg * 2 + wm) * 2 + h) * BN + wn * NB * 16 + nb * 16 + lane] = part[nb][h];
-    }
-    __syncthreads();
-    const int o = n0 + tid;
-    if (tid < BN && o < d_out) {
-      float q[4];  // column o's sums over each 64 rows of i
-#pragma unroll
-      for (int h = 0; h < 4; ++h) {
-        q[h] = s_sum[h * BN + tid];
-        if constexpr (KS == 2) q[h] += s_sum[(4 + h) * BN + tid];
-      }
-      if constexpr (G <= 128) {
-        const int v = m0 / G;
-#pragma unroll
-        for (int a = 0; a < 256 / G; ++a)
-          if (v + a < G_in) dgate[int64_t(o) * G_in + v + a] = G == 64 ? q[a] : q[(2 * a) & 3] + q[(2 * a + 1) & 3];
-      } else if constexpr (G == 256) {
-        dgate[int64_t(o) * G_in + m0 / 256] = (q[0] + q[1]) + (q[2] + q[3]);
-      } else {
-        atomicAdd(dgate + int64_t(o) * G_in + m0 / 512, (q[0] + q[1]) + (q[2] + q[3]));
-      }
-    }
-  }
-}
-
 template <int G, int GO>
 __global__ __launch_bounds__(64 * kDgateWaves) void dgate_kernel(const uint16_t* __restrict__ dY, const uint16_t* __restrict__ X,
                                                     const uint16_t* __restrict__ W, int T, int d_in, int d_out,
                                                     float* __restrict__ dgate, uint16_t* __restrict__ dYt, int ldt,
                                                     ListArgs la) {
-  dgate_tile<G, GO, 256, 1>(dY, X, W, T, d_in, d_out, dgate, dYt, ldt, la);
+  __shared__ u32x4 smem[dgate_smem(256, 1)];
+  dgate_tile<G, GO, 256, 1, true>(dY, X, W, T, d_in, d_out, dgate, dYt, ldt, la, int(blockIdx.x), smem);
 }
 
 // 256 x BN tiles, K over two wave groups.
@@ -771,7 +544,8 @@ __global__ __launch_bounds__(64 * kDgateWaves) void dgate_k2_kernel(const uint16
                                                        const uint16_t* __restrict__ W, int T, int d_in, int d_out,
                                                        float* __restrict__ dgate, uint16_t* __restrict__ dYt, int ldt,
                                                        ListArgs la) {
-  dgate_tile<G, GO, BN, 2>(dY, X, W, T, d_in, d_out, dgate, dYt, ldt, la);
+  __shared__ u32x4 smem[dgate_smem(BN, 2)];
+  dgate_tile<G, GO, BN, 2, true>(dY, X, W, T, d_in, d_out, dgate, dYt, ldt, la, int(blockIdx.x), smem);
 }
 
 // Fill n floats with zero (before the order-independent two-tile accumulation).
@@ -982,18 +756,6 @@ __global__ __launch_bounds__(64 * dx_waves(BM, KS)) void dx_kernel(const uint16_
                                              lane, dX, d_in, n0, T, m0, d_in);
 }
 
-// dX of small square groups over the mask rows that keep something in the
-// tile's columns: a list column of 64 input columns (four or two groups) keeps
-// 94 % or 75 % of the rows at half the groups kept, so gathering single rows saves
-// little, and its 64-column tiles move 1.9 times the operand bytes per MFMA of a
-// 256-column tile.
-template <int G, int BM, int BN, int KS>
-__global__ __launch_bounds__(512) void dx_dense_kernel(const uint16_t* __restrict__ dY, const uint16_t* __restrict__ W,
-                                                       const float* __restrict__ mask, int T, int d_in, int d_out,
-                                                       uint16_t* __restrict__ dX) {
-  wt_gemm_masked<G, BM, BN, KS>(dY, d_out, W, d_out, d_in, T, mask, dX);
-}
-
 // ============================================================================ dY^T
 
 // dY [T, d_out] -> dYt [d_out, ldt] (t in [T, ldt) zero).  One 8 x 8 block per thread.
@@ -1174,32 +936,6 @@ hipError_t launch_dx(const uint16_t* dYt, int ldt, const uint16_t* W, const int*
     case DxTile::kPair: GM_DX(64, 256, 1, 1); break;
   }
 #undef GM_DX
-  return hipGetLastError();
-}
-
-hipError_t launch_dx_dense(const uint16_t* dY, const uint16_t* W, const float* mask, int T, int d_in, int d_out, int g,
-                           uint16_t* dX, hipStream_t s) {
-  auto blocks = [&](int bm, int bn) { return int64_t((d_in + bm - 1) / bm) * ((T + bn - 1) / bn); };
-#define GM_DENSE(G, BM, BN, KS)                                                                                  \
-  hipLaunchKernelGGL((dx_dense_kernel<G, BM, BN, KS>), dim3(unsigned(blocks(BM, BN))), dim3(512), 0, s, dY, W, mask, T, \
-                     d_in, d_out, dX)
-  const WtTile tile = dx_dense_tile(T, d_in, d_out);
-#define GM_DENSE_G(G)                        \
-  if (tile == WtTile::k128x128)              \
-    GM_DENSE(G, 128, 128, 2);                \
-  else if (tile == WtTile::k256x128)         \
-    GM_DENSE(G, 256, 128, 2);                \
-  else                                       \
-    GM_DENSE(G, 256, 256, 1);
-  if (g == 16) {
-    GM_DENSE_G(16)
-  } else if (g == 32) {
-    GM_DENSE_G(32)
-  } else {
-    return hipErrorInvalidValue;
-  }
-#undef GM_DENSE_G
-#undef GM_DENSE
   return hipGetLastError();
 }
 

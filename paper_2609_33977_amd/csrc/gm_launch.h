@@ -49,8 +49,9 @@ hipError_t launch_dx(const uint16_t* dYt, int ldt, const uint16_t* W, const int*
                      const float* scales, const int* subbits, const int* colsoft, int T, int d_in, int d_out, int g,
                      uint16_t* dX, hipStream_t s);
 
-hipError_t launch_dx_dense(const uint16_t* dY, const uint16_t* W, const float* mask, int T, int d_in, int d_out, int g,
-                           uint16_t* dX, hipStream_t s);
+// dX (and dgate, unless null) where dx_dense_ok.
+hipError_t launch_square_bwd(const uint16_t* dY, const uint16_t* X, const uint16_t* W, const float* mask, int T, int d_in,
+                             int d_out, int g, uint16_t* dX, float* dgate, hipStream_t s);
 
 // Distillation loss (Sec. 2.4, Eq. 4) through the LM head.
 int distill_vocab_tiles(int V);

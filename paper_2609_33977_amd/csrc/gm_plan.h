@@ -167,9 +167,47 @@ inline WtTile wt_tile_of(int64_t m, int64_t n, int64_t big, int64_t half, int64_
 // per K slice for 256 x 256, 11 + 0.45 for 256 x 128, 7 + 0.24 for 128 x 128;
 // 4096 x 4096, 32 x 32 groups: T = 4096 101 / 127 / 150 us, T = 2048 97 / 69 /
 // 78, T = 512 88 / 60 / 37).
-inline WtTile dx_dense_tile(int64_t T, int64_t d_in, int64_t d_out) {
+inline int64_t dx_dense_ns(WtTile tile, int64_t d_out) {  // of one block
   const int64_t slices = (d_out + 31) / 32;
-  return wt_tile_of(d_in, T, 10000 + 700 * slices, 11000 + 450 * slices, 7000 + 240 * slices);
+  return tile == WtTile::k256x256 ? 10000 + 700 * slices : tile == WtTile::k256x128 ? 11000 + 450 * slices : 7000 + 240 * slices;
+}
+inline WtTile dx_dense_tile(int64_t T, int64_t d_in, int64_t d_out) {
+  return wt_tile_of(d_in, T, dx_dense_ns(WtTile::k256x256, d_out), dx_dense_ns(WtTile::k256x128, d_out),
+                    dx_dense_ns(WtTile::k128x128, d_out));
+}
+
+// Time until n1 blocks of t1 ns and then n2 of t2, one per CU and each on the first free CU, have ended: the first
+// kind leaves 256 - r CUs free at `free` and r one block later; the end is one of theirs plus whole blocks of t2.
+inline int64_t two_kinds_ns(int64_t n1, int64_t t1, int64_t n2, int64_t t2) {
+  const int64_t r = n1 % 256, free = n1 / 256 * t1;
+  int64_t best = INT64_MAX;
+  for (int late = 0; late < 2; ++late) {
+    const int64_t from = late ? free + t1 : free;
+    auto done = [&](int64_t k) {  // blocks ended by from + k t2
+      const int64_t end = from + k * t2;
+      return (256 - r) * ((end - free) / t2) + (end > free + t1 ? r * ((end - free - t1) / t2) : 0);
+    };
+    int64_t lo = 0, hi = n2;  // (n2 on one CU are done by n2 t2)
+    while (lo < hi) {
+      const int64_t mid = (lo + hi) / 2;
+      if (done(mid) >= n2) hi = mid; else lo = mid + 1;
+    }
+    const int64_t end = from + lo * t2;
+    if (end < best) best = end;
+  }
+  return best > free + (r ? t1 : 0) ? best : free + (r ? t1 : 0);
+}
+
+// dX and dgate of those groups share a launch: whether the dX tiles go first.  4096 x 11008, T = 2048, 32 x 32 groups
+// half kept: 327 us dX first, 367 dgate first (in two launches 364); 4096 x 4096, T = 512 51, 64 (66); 11008 x 4096, T =
+// 1024, equal by this estimate, 220, 203 (204).
+inline bool square_dx_first(int64_t T, int64_t d_in, int64_t d_out, int32_t g) {
+  const WtTile tile = dx_dense_tile(T, d_in, d_out);
+  const int64_t bm = tile == WtTile::k128x128 ? 128 : 256, bn = tile == WtTile::k256x256 ? 256 : 128;
+  const int64_t cols = dgate_columns(T, d_in, d_out, g), sl = (T + 31) / 32;
+  const int64_t nx = tile_blocks(d_in, T, bm, bn), tx = dx_dense_ns(tile, d_out);
+  const int64_t nd = tile_blocks(d_in, d_out, 256, cols), td = 13000 + (cols == 256 ? 620 : 415) * sl;
+  return two_kinds_ns(nx, tx, nd, td) < two_kinds_ns(nd, td, nx, tx);
 }
 
 // The tile with the fewest estimated rounds of 256 blocks times the time per

@@ -285,19 +285,17 @@ __device__ __forceinline__ void wt_gemm(const uint16_t* __restrict__ B, int ldb,
 // (pairs of 16-row entries most), so it is taken where it drops at least one
 // mask row in 16.  4096 x 4096, T = 2048, 32 x 32 groups, us with the walk / with
 // every slice: 3 % kept 26 / 65, 10 % 47 / 65, 20 % 59 / 65, half kept 66 (no
-// walk); 16 x 16: 38 / 66, 61 / 66, 66, 67.  Skipping the MFMAs of a pruned
+// walk); 16 x 16: 38 / 66, 61 / 66, 20 % 66 (no walk).  Skipping the MFMAs of a pruned
 // fragment as well was 5-20 % slower from 30 % kept on and level below; narrower
 // tiles of the same block (half the columns each, over their own rows) gained
 // 4-15 % below 20 % kept in the 256 x 128 tile and lost in the others.
 template <int G, int BM, int BN, int KS>
 __device__ __forceinline__ void wt_gemm_masked(const uint16_t* __restrict__ B, int ldb, const uint16_t* __restrict__ W,
                                                int K, int d, int N, const float* __restrict__ mask,
-                                               uint16_t* __restrict__ out) {
-  __shared__ u32x4 smem[wt_smem(BM, BN, KS)];
-  __shared__ WtMask sm;
-  __shared__ float s_msoft[wt_stages(BM, BN, KS) * 512];
+                                               uint16_t* __restrict__ out, int bid, int blocks, u32x4* smem, WtMask& sm,
+                                               float* s_msoft) {
   int tm, tn;
-  tile_coords(gridDim.x, (d + BM - 1) / BM, (N + BN - 1) / BN, tm, tn);
+  tile_coords(bid, blocks, (d + BM - 1) / BM, (N + BN - 1) / BN, tm, tn);
   const bool soft = wt_mask<G, BM>(mask, K / G, d / G, tm * BM, sm);
   if (sm.nlist * 16 < K / G * 15)
     wt_tile<G, BM, BN, KS, true>(B, ldb, W, K, d, N, mask, out, smem, &sm, s_msoft, tm * BM, tn * BN, soft);

@@ -1,6 +1,8 @@
 """The tile tests name the kernel that each of their shapes runs: the names are checked here against the library's own
 selection (gm_plan.h, compiled for the host), and together they name every tile there is."""
+import heapq
 import os
+import random
 import shutil
 import subprocess
 
@@ -73,3 +75,25 @@ def test_split_tiles(plan):
     s = split.SHAPES
     _check(s, [x[5] for x in s], plan([("fwd", *x[:5], x[6]) for x in s]))
     assert any(x[5] == "128x128 split" for x in s)
+
+
+def test_end_of_a_launch_of_two_kinds_of_blocks(plan):
+    # the closed form against 256 CUs that each take the next block when free
+    r = random.Random(5)
+    rows = [(r.randint(1, 1500), r.randint(1000, 200000), r.randint(1, 1500), r.randint(1000, 200000)) for _ in range(300)]
+    rows += [(256, 5000, 256, 7000), (512, 5000, 1, 7000), (1, 9000, 1, 1000)]
+    got = plan([("kinds", *x, 0, 0) for x in rows])
+    for (n1, t1, n2, t2), g in zip(rows, got):
+        free = [0] * 256
+        end = 0
+        for k in range(n1 + n2):
+            t = heapq.heappop(free) + (t1 if k < n1 else t2)
+            heapq.heappush(free, t)
+            end = max(end, t)
+        assert int(g) == end
+
+
+def test_square_backward_takes_both_orders(plan):
+    # the shapes of the parity tests run dX first and dgate first
+    s = [x for x in backward.DX_TILES if x[5].startswith("dense")]
+    assert set(plan([("first", *x[:5], 0) for x in s])) == {"dX", "dgate"}

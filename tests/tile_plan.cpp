@@ -20,6 +20,10 @@ int main() {
     } else if (!std::strcmp(op, "dx")) {
       if (gm::dx_dense_ok(d_out, int(g))) std::printf("dense %s\n", wt[int(gm::dx_dense_tile(T, d_in, d_out))]);
       else std::printf("%s\n", dx[int(gm::dx_tile(T, d_in, d_out, int(g)))]);
+    } else if (!std::strcmp(op, "kinds")) {  // T blocks of d_in ns, then d_out of g
+      std::printf("%ld\n", long(gm::two_kinds_ns(T, d_in, d_out, g)));
+    } else if (!std::strcmp(op, "first")) {
+      std::printf("%s\n", gm::square_dx_first(T, d_in, d_out, int(g)) ? "dX" : "dgate");
     } else if (!std::strcmp(op, "lm")) {  // T: tokens, d_in: hidden size
       std::printf("%s\n", wt[int(gm::lm_bwd_tile(T, d_in))]);
     } else {
