@@ -49,7 +49,7 @@ DX_TILES = [
     (140, 320, 336, 16, 16, "dense 128x128"),  # K not a multiple of 32, columns past the last tile
     (257, 576, 96, 32, 32, "dense 128x128"),
     (1100, 4096, 160, 32, 32, "dense 128x128"),
-    (17, 4096, 2080, 32, 32, "dense 128x128"),  # dX before dgate in their common launch
+    (17, 4096, 2048, 32, 32, "dense 128x128"),  # dX before dgate in their common launch
     (2041, 4096, 160, 32, 32, "dense 256x128"),
     (2041, 4096, 144, 16, 16, "dense 256x128"),
     (4090, 4096, 96, 32, 32, "dense 256x256"),
