@@ -580,9 +580,12 @@ static hipError_t gemv_passes(const uint16_t* X, const uint16_t* W, const float*
 // blocks) and two of these hold: more than 8 tokens (X is read half as often),
 // in place, few selectors staged (15360 x 5120, 32-row / 64-row blocks: T = 16
 // 23.8 / 21.6 in place, 25.8 / 24.0 packed; T = 8 20.7 / 20.3 and 23.1 / 23.7; 64
-// groups wide T = 8 22.4 / 23.7); beyond one round where all three hold and the
-// last round is well filled (27648 x 5120, T = 16 in place 40.6 / 39.9).  32
-// rows otherwise (27648 x 5120, T = 8: 35.2 / 37.8, packed 40.5 / 45.1).
+// groups wide T = 8 22.4 / 23.7).  Beyond one round, 64 rows in place with few
+// selectors, 14 tokens or more of at least 5120 columns, and a last round well
+// filled: 16 tokens, 32 / 64 rows, 27648 x 5120 38.6 / 38.1, 30720 x 6144 52.5 /
+// 50.1, 27648 x 13824 96 / 88; but 4096 columns 34.7 / 35.5, 12 tokens of 5120 37.0
+// / 37.3, a last round half full (24576 x 5120) 38.1 / 39.7, 14 % full 31.5 / 36.4.
+// 32 rows otherwise (27648 x 5120, T = 8: 35.2 / 37.8, packed 40.5 / 45.1).
 template <bool PACKED>
 static bool launch_mfma(const uint16_t* X, const uint16_t* W, const float* mask, const int* chunk, const float* scale,
                         const int* rowptr, int T, int d_in, int d_out, int g, int go, uint16_t* Y, hipStream_t s,
@@ -592,7 +595,7 @@ static bool launch_mfma(const uint16_t* X, const uint16_t* W, const float* mask,
   auto fits = [&](int R) { return table(R) <= kMmaMaskFloats; };
   const int b64 = (d_out + 63) / 64;
   const int votes = int(T > 8) + int(!PACKED) + int(table(64) <= 2048);
-  const bool rows64 = b64 > 256 ? votes == 3 && (b64 - 1) % 256 >= 160 : b64 >= 192 && votes >= 2;
+  const bool rows64 = b64 > 256 ? votes == 3 && T >= 14 && d_in >= 5120 && (b64 - 1) % 256 >= 160 : b64 >= 192 && votes >= 2;
   int rt = (d_out + 15) / 16 <= 256 ? 1 : rows64 ? 4 : 2;
   while (rt > 1 && !fits(16 * rt)) rt /= 2;
   // byte offsets into the block's rows of W (or its pieces) and into X are 32-bit, below the out-of-range marker

@@ -19,7 +19,8 @@ pytestmark = pytest.mark.gpu
     (12, 8256, 4104, 64),
     (8, 512, 12296, 256),    # 64-row blocks in place, 32-row packed
     (16, 512, 16392, 256),   # just past one round of 64-row blocks
-    (16, 512, 26632, 256),   # a second round that is well filled: 64-row blocks in place
+    (16, 512, 26632, 256),   # a second round
+    (14, 5120, 26632, 256),  # ... well filled, of long rows: 64-row blocks in place
 ])
 def test_decode_blocks(T, d_in, d_out, g):
     import torch
