@@ -188,8 +188,10 @@ __global__ __launch_bounds__(64 * kFwdWaves) void fwd_kernel(const uint16_t* __r
       packed_rows(X, W, pk.chunk, pk.scale, pk.rowptr, m0 + wave, m0 + rows, NW, n0, min(n0 + BN, T), d_in, d_out, G, lane, Y);
       return;
     }
-    if (tid % TPR == 0 && r < rows) {
-      int at = rp0 - p0;
+    if (tid % TPR == 0) {
+      // (rows past d_out: base 0, so that the offsets of their pruned chunks stay far from 2^32, where the copy's
+      // instruction offset could wrap them into range)
+      int at = r < rows ? rp0 - p0 : 0;
       for (int w = 0; w < words; ++w) {
         const uint32_t b = s_bits[r][w];
         s_base[r][w] = at;
@@ -333,15 +335,15 @@ __global__ __launch_bounds__(64 * kFwdWaves) void fwd_kernel(const uint16_t* __r
   if constexpr (PACKED) rA = make_rsrc_grouped(W + int64_t(p0) * G, bytesW);
   auto prepare = [&](int st) {
     const bool live = st < ng;
+    const uint32_t past = live ? 0u : kOOB;
     const int sub = (st + s0) % SUB;
 #pragma unroll
     for (int j = 0; j < CA; ++j) {
       const int gr = group_of(v_cur, j);
       const uint32_t dead = ((~bits_cur[j] >> (gr & 31)) & 1u) << 31;
-      if constexpr (PACKED)  // (rows past d_out have no base: their offsets are replaced, not flagged)
-        curA[j] = live && !dead ? group_voffset(uint32_t(piece_of(bits_cur[j], base_cur[j], gr)) * uint32_t(2 * G) +
-                                                    uint32_t(sub * kBK * 2) + offA[j], j)
-                                : kOOB;
+      if constexpr (PACKED)
+        curA[j] = group_voffset(uint32_t(piece_of(bits_cur[j], base_cur[j], gr)) * uint32_t(2 * G) +
+                                    uint32_t(sub * kBK * 2) + offA[j], j) | dead | past;
       else
         curA[j] = offA[j] | dead;
     }
