@@ -372,7 +372,8 @@ GM_EXPORT gm_status gm_masked_linear_fwd(const uint16_t* X, const uint16_t* W, c
 namespace {
 
 // The backward after argument validation: column lists, dgate (with the dY^T
-// side output when dX is wanted), dX.  `ws` holds at least bwd_layout().total
+// side output when dX is wanted), dX; one launch without lists or dY^T for
+// 16 x 16 and 32 x 32 groups of up to kWtMaskRows mask rows.  `ws` holds at least bwd_layout().total
 // bytes when dX is wanted.
 gm_status masked_linear_bwd_launch(const uint16_t* dY, const uint16_t* X, const uint16_t* W, const float* mask,
                                    int64_t T, int64_t d_in, int64_t d_out, int32_t g, int32_t g_out, uint16_t* dX,

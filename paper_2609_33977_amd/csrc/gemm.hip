@@ -839,10 +839,10 @@ hipError_t launch_fwd(const uint16_t* X, const uint16_t* W, const float* mask, i
   return hipGetLastError();
 }
 
-// Forward from the packed export (more than 16 tokens).  The four stacked
-// LLaMA-2-13B projections of a layer at T = 512, half the groups kept: 0.42 ms
-// against 9.4 ms for one wave per row and 16 tokens; a tile takes 2-15 % longer
-// than in place (the pieces' offsets instead of a fixed row stride).
+// Forward from the packed export (more than 16 tokens, where packed_passes does
+// not send them through the 2-16 token kernel).  The four stacked LLaMA-2-13B
+// projections of a layer at T = 512, half the groups kept: 0.41 ms against
+// 9.4 ms for one wave per row and 16 tokens.
 hipError_t launch_fwd_packed(const uint16_t* X, const uint16_t* Wp, const int* chunk, const float* scale,
                              const int* rowptr, int T, int d_in, int d_out, int g, uint16_t* Y, FwdTile tile,
                              hipStream_t s) {

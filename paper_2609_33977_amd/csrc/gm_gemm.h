@@ -75,7 +75,7 @@ struct AllRows {
   __device__ uint32_t operator()(int) const { return ~0u; }
 };
 
-// The K-loop shared by the three GEMMs.  `prepare(st)` computes whatever the
+// The K-loop shared by the GEMMs.  `prepare(st)` computes whatever the
 // copies of K slice st need (buffer resources, per-lane offsets); it is called
 // once per slice, in increasing st, at a point where this wave has no LDS read
 // in flight, so any LDS or scalar loads it makes cost only their own latency.
